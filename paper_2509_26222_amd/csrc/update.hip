@@ -520,8 +520,8 @@ __device__ inline void acc_to_lds(const Acc64& A, double (*T)[LDT]) {
       for (int v = 0; v < 4; ++v) T[acc_row(mi, v)][acc_col(ni)] = A.c[mi][ni][v];
 }
 
-// In-place Cholesky of the lower triangle of T (64x64) and Tinv = L^{-1}:
-// chol64() in chol64.hpp.
+// L^{-1} of one 64x64 block: chol64() in chol64.hpp; PHASED below: the form
+// of the low-precision products, chol64_phased().
 #include "chol64.hpp"
 
 // Blocks of the inverse X = L^{-1} of the blocked factor, row by row:
@@ -627,23 +627,29 @@ __global__ void __launch_bounds__(256) k_linv_row(int32_t Bp, int32_t kb,
 }
 
 // Factor diagonal block 0.
+template <bool PHASED>
 __device__ __forceinline__ void chol_first_body(const double* __restrict__ S, int32_t Bp,
-    double* __restrict__ Lb, double* __restrict__ Linv, double* __restrict__ LiT,
-    int32_t* __restrict__ status, int64_t batch, int64_t seq) {
+    double* __restrict__ Linv, double* __restrict__ LiT, int32_t* __restrict__ status,
+    int64_t batch, int64_t seq) {
   if (seq_skip(status, seq)) return;
-  __shared__ double T[NB][LDT], Ti[NB][LDT];
+  __shared__ double T[NB][LDT];
   load_tile(T, S, Bp);
   __syncthreads();
-  chol64(T, Ti, status, batch, seq);
-  store_tile(T, Lb, Bp);
-  store_tile(Ti, Linv, NB);
-  if (LiT) store_tile_t(Ti, LiT, Bp);
+  if constexpr (PHASED) {
+    __shared__ double Ti[NB][LDT];
+    chol64_phased(T, Ti, status, batch, seq);
+    store_tile(Ti, Linv, NB);
+    if (LiT) store_tile_t(Ti, LiT, Bp);
+  } else {
+    chol64(T, Linv, LiT, Bp, status, batch, seq);
+  }
 }
 
+template <bool PHASED>
 __global__ void __launch_bounds__(256) k_chol_first(const double* __restrict__ S, int32_t Bp,
-    double* __restrict__ Lb, double* __restrict__ Linv, double* __restrict__ LiT,
-    int32_t* __restrict__ status, int64_t batch, int64_t seq) {
-  chol_first_body(S, Bp, Lb, Linv, LiT, status, batch, seq);
+    double* __restrict__ Linv, double* __restrict__ LiT, int32_t* __restrict__ status,
+    int64_t batch, int64_t seq) {
+  chol_first_body<PHASED>(S, Bp, Linv, LiT, status, batch, seq);
 }
 
 // The diagonal workgroup of step kb (the launch's critical path), with Ta =
@@ -674,11 +680,12 @@ __device__ inline void chol_diag_prefetch(const double* __restrict__ S, int32_t 
   }
 }
 
+template <bool PHASED>
 __device__ inline void chol_step_diag(const double (&aii)[3][4], int32_t Bp, int i,
-                                      double* __restrict__ Lb, double* __restrict__ Linv,
-                                      double* __restrict__ LiT, double (*Ta)[LDT],
-                                      double (*Tb)[LDT], int32_t* __restrict__ status,
-                                      int64_t batch, int64_t seq) {
+                                      double* __restrict__ Linv, double* __restrict__ LiT,
+                                      double (*Ta)[LDT], double (*Tb)[LDT],
+                                      int32_t* __restrict__ status, int64_t batch,
+                                      int64_t seq) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 15, kq = lane >> 4;
   v4d l[4];
@@ -717,12 +724,17 @@ __device__ inline void chol_step_diag(const double (&aii)[3][4], int32_t Bp, int
     }
   }
   __syncthreads();
-  // the strictly upper blocks of Tb still hold A_ik; the factor clears them
-  // without reading them
-  chol64(Tb, Ta, status, batch, seq);
-  store_tile(Tb, Lb + (int64_t)i * NB * Bp + (int64_t)i * NB, Bp);
-  store_tile(Ta, Linv + (int64_t)i * NB * NB, NB);
-  if (LiT) store_tile_t(Ta, LiT + (int64_t)i * NB * Bp + (int64_t)i * NB, Bp);
+  // the strictly upper blocks of Tb still hold A_ik; the factor does not read
+  // them
+  double* Li = Linv + (int64_t)i * NB * NB;
+  double* Lt = LiT ? LiT + (int64_t)i * NB * Bp + (int64_t)i * NB : nullptr;
+  if constexpr (PHASED) {
+    chol64_phased(Tb, Ta, status, batch, seq);
+    store_tile(Ta, Li, NB);
+    if (Lt) store_tile_t(Ta, Lt, Bp);
+  } else {
+    chol64(Tb, Li, Lt, Bp, status, batch, seq);
+  }
 }
 
 // Step kb of the right-looking blocked Cholesky, one launch per block
@@ -733,6 +745,7 @@ __device__ inline void chol_step_diag(const double (&aii)[3][4], int32_t Bp, int
 // launch also carries the inverse's work of step kb (linv_work: kb + kb *
 // (nblk - 1 - kb) workgroups of one or two block products), beside the
 // critical path of the factor.
+template <bool PHASED>
 __device__ __forceinline__ void chol_step_body(double* __restrict__ S, int32_t Bp, int32_t nblk,
     int32_t kb, double* __restrict__ Lb, double* __restrict__ Linv, double* __restrict__ LiT,
     int32_t* __restrict__ status, int64_t batch, int64_t seq) {
@@ -769,7 +782,7 @@ __device__ __forceinline__ void chol_step_body(double* __restrict__ S, int32_t B
   load_tile(Tb, S + (int64_t)i * NB * Bp + (int64_t)kb * NB, Bp);
   __syncthreads();
   if (diag) {
-    chol_step_diag(aii, Bp, i, Lb, Linv, LiT, Ta, Tb, status, batch, seq);
+    chol_step_diag<PHASED>(aii, Bp, i, Linv, LiT, Ta, Tb, status, batch, seq);
     return;
   }
   Acc64 A;
@@ -810,10 +823,11 @@ __device__ __forceinline__ void chol_step_body(double* __restrict__ S, int32_t B
         Aij[(int64_t)acc_row(mi, v) * Bp + acc_col(ni)] -= U.c[mi][ni][v];
 }
 
+template <bool PHASED>
 __global__ void __launch_bounds__(256, 2) k_chol_step(double* __restrict__ S, int32_t Bp,
     int32_t nblk, int32_t kb, double* __restrict__ Lb, double* __restrict__ Linv,
     double* __restrict__ LiT, int32_t* __restrict__ status, int64_t batch, int64_t seq) {
-  chol_step_body(S, Bp, nblk, kb, Lb, Linv, LiT, status, batch, seq);
+  chol_step_body<PHASED>(S, Bp, nblk, kb, Lb, Linv, LiT, status, batch, seq);
 }
 
 // ----------------------------------------------------------------- TRSM
@@ -1109,15 +1123,16 @@ rbf_status update_workspace(rbf_ctx* ctx, int64_t N, int32_t kmax, int64_t Bmax,
   return RBF_OK;
 }
 
-rbf_status chol_blocked(rbf_ctx* ctx, double* S, int32_t n, double* Lb, double* Linv,
-                        int64_t index, int64_t seq, double* LiT) {
+template <bool PHASED>
+static rbf_status chol_blocked_t(rbf_ctx* ctx, double* S, int32_t n, double* Lb, double* Linv,
+                                 int64_t index, int64_t seq, double* LiT) {
   const int32_t nblk = n / NB;
-  k_chol_first<<<1, 256, 0, ctx->stream>>>(S, n, Lb, Linv, LiT, ctx->d_status, index, seq);
+  k_chol_first<PHASED><<<1, 256, 0, ctx->stream>>>(S, n, Linv, LiT, ctx->d_status, index, seq);
   RBF_LAUNCHED(ctx, "k_chol_first");
   for (int32_t kb = 0; kb + 1 < nblk; ++kb) {
     const int m = nblk - kb - 1;
     const int extra = LiT ? kb + kb * (nblk - 1 - kb) : 0;
-    k_chol_step<<<m + m * (m + 1) / 2 + extra, 256, 0, ctx->stream>>>(
+    k_chol_step<PHASED><<<m + m * (m + 1) / 2 + extra, 256, 0, ctx->stream>>>(
         S, n, nblk, kb, Lb, Linv, LiT, ctx->d_status, index, seq);
     RBF_LAUNCHED(ctx, "k_chol_step");
   }
@@ -1127,6 +1142,13 @@ rbf_status chol_blocked(rbf_ctx* ctx, double* S, int32_t n, double* Lb, double* 
     RBF_LAUNCHED(ctx, "k_linv_row");
   }
   return RBF_OK;
+}
+
+rbf_status chol_blocked(rbf_ctx* ctx, double* S, int32_t n, double* Lb, double* Linv,
+                        int64_t index, int64_t seq, double* LiT, rbf_prec prec) {
+  return prec == RBF_F64
+             ? chol_blocked_t<false>(ctx, S, n, Lb, Linv, index, seq, LiT)
+             : chol_blocked_t<true>(ctx, S, n, Lb, Linv, index, seq, LiT);
 }
 
 // Single right-hand side (x of nblk*64 entries, contiguous): one workgroup
@@ -1373,7 +1395,7 @@ rbf_status update_run(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g,
     double* Vt = VtB[bi & 1];
     prof_begin(ctx, RBF_PROF_CHOL);
     RBF_TRY(fill_zero(ctx, ws.LiT, sizeof(double) * (size_t)Bpc * Bpc));
-    RBF_TRY(chol_blocked(ctx, S, Bpc, Lb, Linv, ctx->index_base + bi, sq, ws.LiT));
+    RBF_TRY(chol_blocked(ctx, S, Bpc, Lb, Linv, ctx->index_base + bi, sq, ws.LiT, gemm_prec));
     prof_end(ctx, RBF_PROF_CHOL);
     prof_begin(ctx, RBF_PROF_TRSM);
     RBF_TRY(linv_apply(ctx, ws.LiT, Bpc, Ut, ldu, N + 1, Vt, sq));
@@ -1532,9 +1554,10 @@ __global__ void __launch_bounds__(256) k_zero_lit_g(const GJob* __restrict__ job
     *reinterpret_cast<double2*>(J.LiT + e0 + u) = make_double2(0.0, 0.0);
 }
 
+template <bool PHASED>
 __global__ void __launch_bounds__(256) k_chol_first_g(const GJob* __restrict__ jobs) {
   const GJob& J = jobs[blockIdx.z];
-  chol_first_body(J.S, J.Bp, J.Lb, J.Linv, J.LiT, J.status, J.index, J.seq);
+  chol_first_body<PHASED>(J.S, J.Bp, J.Linv, J.LiT, J.status, J.index, J.seq);
 }
 
 // Split form of Cholesky step kb, for launches over many factors (the
@@ -1548,6 +1571,7 @@ __global__ void __launch_bounds__(256) k_chol_first_g(const GJob* __restrict__ j
 // operations in the same order as in chol_step_body (the stored panel holds
 // the same accumulator values the fused tile forms), so the factor is the
 // same bit for bit.
+template <bool PHASED>
 __device__ __forceinline__ void chol_panel_body(double* __restrict__ S, int32_t Bp,
     int32_t nblk, int32_t kb, double* __restrict__ Lb, double* __restrict__ Linv,
     double* __restrict__ LiT, int32_t* __restrict__ status, int64_t batch, int64_t seq) {
@@ -1567,7 +1591,7 @@ __device__ __forceinline__ void chol_panel_body(double* __restrict__ S, int32_t 
   load_tile(Tb, S + (int64_t)i * NB * Bp + (int64_t)kb * NB, Bp);
   __syncthreads();
   if (diag) {
-    chol_step_diag(aii, Bp, i, Lb, Linv, LiT, Ta, Tb, status, batch, seq);
+    chol_step_diag<PHASED>(aii, Bp, i, Linv, LiT, Ta, Tb, status, batch, seq);
     return;
   }
   Acc64 A;
@@ -1622,11 +1646,12 @@ __host__ __device__ inline int32_t chol_trail_groups(int32_t Bp, int32_t kb) {
   return m <= 0 ? 0 : m * (m + 1) / 2 - 1;
 }
 
+template <bool PHASED>
 __global__ void __launch_bounds__(256, 2) k_chol_panel_g(const GJob* __restrict__ jobs,
                                                          int32_t kb) {
   const GJob& J = jobs[blockIdx.z];
   if ((int32_t)blockIdx.x >= chol_panel_groups(J.Bp, kb)) return;
-  chol_panel_body(J.S, J.Bp, J.Bp / NB, kb, J.Lb, J.Linv, J.LiT, J.status, J.index, J.seq);
+  chol_panel_body<PHASED>(J.S, J.Bp, J.Bp / NB, kb, J.Lb, J.Linv, J.LiT, J.status, J.index, J.seq);
 }
 
 __global__ void __launch_bounds__(256, 2) k_chol_trail_g(const GJob* __restrict__ jobs,
@@ -1636,11 +1661,12 @@ __global__ void __launch_bounds__(256, 2) k_chol_trail_g(const GJob* __restrict_
   chol_trail_body(J.S, J.Bp, J.Bp / NB, kb, J.Lb, J.status, J.seq);
 }
 
+template <bool PHASED>
 __global__ void __launch_bounds__(256, 2) k_chol_step_g(const GJob* __restrict__ jobs,
                                                         int32_t kb) {
   const GJob& J = jobs[blockIdx.z];
   if ((int32_t)blockIdx.x >= chol_step_groups(J.Bp, kb)) return;
-  chol_step_body(J.S, J.Bp, J.Bp / NB, kb, J.Lb, J.Linv, J.LiT, J.status, J.index, J.seq);
+  chol_step_body<PHASED>(J.S, J.Bp, J.Bp / NB, kb, J.Lb, J.Linv, J.LiT, J.status, J.index, J.seq);
 }
 
 __global__ void __launch_bounds__(256) k_linv_row_g(const GJob* __restrict__ jobs) {
@@ -1661,23 +1687,24 @@ __global__ void __launch_bounds__(256) k_upd_w_sum_g(const GJob* __restrict__ jo
   upd_w_sum_body(J.w, J.wpart, J.N, (J.Bc + 63) / 64, J.status, J.seq);
 }
 
-rbf_status chol_grouped(rbf_ctx* ctx, const GRound& r) {
+template <bool PHASED>
+static rbf_status chol_grouped_t(rbf_ctx* ctx, const GRound& r) {
   if (r.n <= 0) return RBF_OK;
   const unsigned nz = (unsigned)r.n;
   hipStream_t s = ctx->stream;
   k_zero_lit_g<<<dim3(r.zero_x, 1, nz), 256, 0, s>>>(r.jobs);
   RBF_LAUNCHED(ctx, "k_zero_lit_g");
-  k_chol_first_g<<<dim3(1, 1, nz), 256, 0, s>>>(r.jobs);
+  k_chol_first_g<PHASED><<<dim3(1, 1, nz), 256, 0, s>>>(r.jobs);
   RBF_LAUNCHED(ctx, "k_chol_first_g");
   for (int32_t kb = 0; kb < r.nsteps; ++kb) {
     // the fused step's workgroup count bounds both split launches' counts
     if (r.chol_split) {
-      k_chol_panel_g<<<dim3(r.step_x[kb], 1, nz), 256, 0, s>>>(r.jobs, kb);
+      k_chol_panel_g<PHASED><<<dim3(r.step_x[kb], 1, nz), 256, 0, s>>>(r.jobs, kb);
       RBF_LAUNCHED(ctx, "k_chol_panel_g");
       k_chol_trail_g<<<dim3(r.step_x[kb], 1, nz), 256, 0, s>>>(r.jobs, kb);
       RBF_LAUNCHED(ctx, "k_chol_trail_g");
     } else {
-      k_chol_step_g<<<dim3(r.step_x[kb], 1, nz), 256, 0, s>>>(r.jobs, kb);
+      k_chol_step_g<PHASED><<<dim3(r.step_x[kb], 1, nz), 256, 0, s>>>(r.jobs, kb);
       RBF_LAUNCHED(ctx, "k_chol_step_g");
     }
   }
@@ -1686,6 +1713,10 @@ rbf_status chol_grouped(rbf_ctx* ctx, const GRound& r) {
     RBF_LAUNCHED(ctx, "k_linv_row_g");
   }
   return RBF_OK;
+}
+
+rbf_status chol_grouped(rbf_ctx* ctx, const GRound& r, rbf_prec prec) {
+  return prec == RBF_F64 ? chol_grouped_t<false>(ctx, r) : chol_grouped_t<true>(ctx, r);
 }
 
 rbf_status update_round_grouped(rbf_ctx* ctx, const GRound& r, rbf_prec prec) {
@@ -1708,7 +1739,7 @@ rbf_status update_round_grouped(rbf_ctx* ctx, const GRound& r, rbf_prec prec) {
   }
   k_upd_S_g<<<dim3(r.s_x, r.s_y, nz), 256, 0, s>>>(r.jobs);
   RBF_LAUNCHED(ctx, "k_upd_S_g");
-  RBF_TRY(chol_grouped(ctx, r));
+  RBF_TRY(chol_grouped(ctx, r, prec));
   RBF_TRY(linv_apply_grouped(ctx, r));
   k_upd_w_part_g<<<dim3(r.wp_x, r.wp_y, nz), 256, 0, s>>>(r.jobs);
   RBF_LAUNCHED(ctx, "k_upd_w_part_g");

@@ -105,9 +105,11 @@ rbf_status update_workspace(rbf_ctx* ctx, int64_t N, int32_t kmax, int64_t Bmax,
 // its off-diagonal 64x64 blocks in Lb (n x n, leading dimension n) and the
 // inverses of its diagonal blocks in Linv ((n/64) x 64 x 64). A breakdown
 // records RBF_E_NOT_SPD with `index` in the status word. Launches belong to
-// launch group seq.
+// launch group seq. prec: precision of the covariance products the factor
+// serves; for FP32 and BF16 the 64x64 blocks take chol64_phased.
 rbf_status chol_blocked(rbf_ctx* ctx, double* S, int32_t n, double* Lb, double* Linv,
-                        int64_t index, int64_t seq, double* LiT = nullptr);
+                        int64_t index, int64_t seq, double* LiT = nullptr,
+                        rbf_prec prec = RBF_F64);
 
 // With LiT (n x n, leading dimension n, zero above the diagonal blocks on
 // entry), chol_blocked also forms X = L^{-1} transposed: LiT[c][r] = X[r][c].
@@ -247,7 +249,7 @@ rbf_status update_round_grouped(rbf_ctx* ctx, const GRound& r, rbf_prec prec);
 // with L^{-1} transposed in LiT, as chol_blocked does for one matrix (uses
 // the jobs' S, Bp, Lb, Linv, LiT, status, index and seq; the round's
 // zero_x, nsteps, step_x and lr_x).
-rbf_status chol_grouped(rbf_ctx* ctx, const GRound& r);
+rbf_status chol_grouped(rbf_ctx* ctx, const GRound& r, rbf_prec prec = RBF_F64);
 
 // The covariance products of a round, and its V^T = L^{-1} U^T (syrk.hip).
 rbf_status syrk_grouped(rbf_ctx* ctx, const GRound& r, rbf_prec prec);
