@@ -244,7 +244,7 @@ static rbf_status batched_build(rbf_batched* b, rbf_ctx* ctx) {
         mx(r.zero_x, ceil_div((int64_t)J.Bp * J.Bp, 4096));
         nsteps = std::max(nsteps, nblk - 1);
         mx(r.lr_x, nblk - 1);
-        mx(r.la_x, ceil_div(J.Bp, SYRK_TILE) * ceil_div(J.ncols, SYRK_TILE));
+        mx(r.la_x, ceil_div(J.Bp, LINV_TILE) * ceil_div(J.ncols, LINV_TILE));
         mx(r.wp_x, ceil_div(J.N, 256));
         mx(r.wp_y, ceil_div(J.Bc, 64));
         mx(r.ws_x, ceil_div(J.N, 256));
@@ -267,7 +267,8 @@ static rbf_status batched_build(rbf_batched* b, rbf_ctx* ctx) {
       pre_main_at[c].push_back(pre.size());
       pre.push_back(0);
       for (size_t j = j0; j < jobs.size(); ++j)
-        pre.push_back(pre.back() + 8 * jobs[j].main_per_xcd);
+        pre.push_back(pre.back() + 8 * jobs[j].main_per_xcd *
+                                       (b->gemm_prec == RBF_F64 ? SYRK_MAIN_WG : 1));
       r.n_main = pre.back();
       pre_tail_at[c].push_back(pre.size());
       pre.push_back(0);

@@ -781,7 +781,7 @@ rbf_status rbf_solve_plan_create(rbf_ctx* ctx, int64_t N, const int64_t* rowptr,
       r.zero_x = std::max<int32_t>(r.zero_x, (int32_t)ceil_div((int64_t)n.kp * n.kp, 4096));
       r.lr_x = std::max(r.lr_x, n.kp / 64 - 1);
       r.la_x = std::max<int32_t>(
-          r.la_x, (int32_t)(ceil_div(n.kp, SYRK_TILE) * ceil_div(n.m, SYRK_TILE)));
+          r.la_x, (int32_t)(ceil_div(n.kp, LINV_TILE) * ceil_div(n.m, LINV_TILE)));
     }
     r.n = (int32_t)(gjobs.size() - job_at.back());
     r.nsteps = nsteps;
@@ -792,7 +792,7 @@ rbf_status rbf_solve_plan_create(rbf_ctx* ctx, int64_t N, const int64_t* rowptr,
     pre_at.push_back(pre.size());
     pre.push_back(0);
     for (size_t j = job_at.back(); j < gjobs.size(); ++j)
-      pre.push_back(pre.back() + 8 * gjobs[j].main_per_xcd);
+      pre.push_back(pre.back() + 8 * gjobs[j].main_per_xcd * SYRK_MAIN_WG);
     r.n_main = pre.back();
     pre.push_back(0);
     for (size_t j = job_at.back(); j < gjobs.size(); ++j)

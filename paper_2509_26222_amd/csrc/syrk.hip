@@ -1,11 +1,11 @@
 // Covariance product P -= V V^T on MFMA (the dominant step of the recursive
 // update, eq. H_inverse_update in Kalman form).
 //
-// V^T (Bc x N) is read as two 128-column panels per 128x128 output tile;
-// only tiles on or below the diagonal are computed and each result is
-// written to both triangles, which keeps P exactly symmetric. Tiles are
-// assigned so that each XCD works through a contiguous run of the tile
-// list (neighbouring tiles share V^T panels in that XCD's L2).
+// V^T (Bc x N) is read as two column panels per output tile; only tiles on
+// or below the diagonal are computed and each result is written to both
+// triangles, which keeps P exactly symmetric. Tiles are assigned so that each
+// XCD works through a contiguous run of the tile list (neighbouring tiles
+// share V^T panels in that XCD's L2).
 //
 // Lane layouts (v_mfma_f64_16x16x4_f64, checked on gfx950):
 //   A[i][k] in lane i + 16k, B[k][j] in lane j + 16k,
@@ -17,8 +17,7 @@ namespace rbf {
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int ST = SYRK_TILE;  // output tile
-constexpr int SKC = 16;     // rows of V^T per LDS stage
-constexpr int SLD = ST + 8; // LDS pitch (doubles)
+constexpr int SYRK_NT = 512;   // threads of a low-precision product's workgroup
 
 __device__ inline void tile_of(int64_t t, int* I, int* J) {
   int i = (int)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
@@ -67,326 +66,260 @@ __device__ inline int64_t xcd_tile(int64_t bid, int64_t per_xcd) {
   return (bid & 7) * per_xcd + (bid >> 3);
 }
 
-// Stage loader of the FP64 product: the 16 x 128 panel slice (rows r0.. of
-// V^T, columns c0..) as 4 double2 per thread; element pair i*256 + tid sits
-// at row (i*256 + tid) / 64, column 2 ((i*256 + tid) % 64), so one wave
-// reads one 1 KB row run and writes it to LDS with 16-byte stores that touch
-// every bank once (zero outside [0, N) x [0, K)).
-// W = 64: the 16 x 64 slice of a 64-column panel, the same way (one wave
-// covers two rows).
-template <int NT, int W = 128>
-__device__ inline void load_stage(const double* __restrict__ Ut, int64_t ldu, int64_t N, int r0,
-                                  int K, int64_t c0, double2 v[16 * W / 2 / NT]) {
-  constexpr int H = W / 2;  // double2 per row
-  const int tid = threadIdx.x;
-  if (r0 + 16 <= K && c0 + W <= N) {  // whole slice inside: no per-load tests
+// ------------------------------------------------------- FP64 products
+//
+// C = A^T B with A and B k-major (row k of either holds its columns), one
+// block of 16 BM x 16 BN per wave, straight from global memory. In this
+// layout both MFMA operand fragments of four rows are whole 128-byte row
+// pieces, so staging them in LDS only adds barriers that all waves of a CU
+// wait at together; the waves of a workgroup take neighbouring blocks and
+// share their panels in L1. What bounds it is FP64 MFMA issue: a wave's
+// vector work does not overlap its own FP64 products (64 cycles each, and
+// about 28 more per switch between the two), so the loop holds none: loads
+// go through buffer resources whose row offset is scalar, in groups of KU
+// k-steps (of 4 rows), NBUF groups ahead, each group's products back to back.
+//
+// Against 128x128 tiles staged in LDS (8 waves of 32x64), V V^T of 1024 rows
+// on random data: 51.1 -> 61.3 TFLOP/s at N = 10,000 (blocks of 64x32),
+// 42.2 -> 56.8 at 5041; blocks of 32x32: 134 -> 115 us at N = 2000, 63 -> 51 us
+// at 1100; blocks of 16x16: 41 -> 19 us at 400. Every element takes its MFMAs
+// in order of k in each of these forms, so their results are the same bit
+// for bit.
+//
+// Rows past K and columns past the width: rows read as zero (out of the
+// resource), columns are read at the operand's last one and their results
+// not stored.
+template <int BM, int BN>
+struct Direct {  // loads in flight per wave, measured per block shape
+  static constexpr int KU = BM * BN >= 8 ? 2 : BM * BN >= 4 ? 1 : 4;
+  static constexpr int NBUF = BM * BN >= 8 ? 3 : BM * BN >= 4 ? 8 : 4;
+  static constexpr int ROWS = 4 * KU * NBUF;  // rows per turn of the loop
+};
+
+// Largest number of rows that one resource covers (32-bit byte offsets).
+__device__ __forceinline__ int direct_segment(int64_t ld) {
+  const int64_t rows = ((int64_t)1 << 31) / (8 * ld) / 768 * 768;  // 768: whole turns
+  return rows > 0 ? (int)min(rows, (int64_t)1 << 20) : 768;
+}
+
+template <int BM, int BN>
+__device__ __forceinline__ void direct_product(const double* __restrict__ A, int64_t lda,
+                                               int64_t na, int64_t a0,
+                                               const double* __restrict__ B, int64_t ldb,
+                                               int64_t nb, int64_t b0, int K,
+                                               v4d (&acc)[BM][BN]) {
+  constexpr int KU = Direct<BM, BN>::KU, NBUF = Direct<BM, BN>::NBUF;
+  constexpr int ROWS = Direct<BM, BN>::ROWS;
+  static_assert(768 % ROWS == 0, "a segment is whole turns");
+  const int lane = threadIdx.x & 63, li = lane & 15, kq = lane >> 4;
+  int va[BM], vb[BN];
 #pragma unroll
-    for (int i = 0; i < 16 * H / NT; ++i) {
-      const int e = i * NT + tid;
-      v[i] = *reinterpret_cast<const double2*>(Ut + (int64_t)(r0 + e / H) * ldu + c0 +
-                                               2 * (e % H));
+  for (int i = 0; i < BM; ++i) va[i] = (int)((kq * lda + min(a0 + 16 * i + li, na - 1)) * 8);
+#pragma unroll
+  for (int j = 0; j < BN; ++j) vb[j] = (int)((kq * ldb + min(b0 + 16 * j + li, nb - 1)) * 8);
+#pragma unroll
+  for (int i = 0; i < BM; ++i)
+#pragma unroll
+    for (int j = 0; j < BN; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
+  const int sa = (int)lda * 32, sb = (int)ldb * 32;  // bytes per k-step
+  const int seg = min(direct_segment(lda), direct_segment(ldb));
+  double fa[NBUF][KU][BM], fb[NBUF][KU][BN];
+  for (int k0 = 0; k0 < K; k0 += seg) {
+    const int rows = min(seg, K - k0);
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(A + k0 * lda), (short)0, (int)(rows * lda * 8), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(B + k0 * ldb), (short)0, (int)(rows * ldb * 8), 0x00020000);
+    auto load = [&](int q, int ks) {
+#pragma unroll
+      for (int s = 0; s < KU; ++s) {
+#pragma unroll
+        for (int i = 0; i < BM; ++i)
+          fa[q][s][i] = __builtin_bit_cast(
+              double, __builtin_amdgcn_raw_buffer_load_b64(ra, va[i], (ks + s) * sa, 0));
+#pragma unroll
+        for (int j = 0; j < BN; ++j)
+          fb[q][s][j] = __builtin_bit_cast(
+              double, __builtin_amdgcn_raw_buffer_load_b64(rb, vb[j], (ks + s) * sb, 0));
+      }
+    };
+#pragma unroll
+    for (int q = 0; q < NBUF; ++q) load(q, KU * q);
+    const int turns = (rows + ROWS - 1) / ROWS;
+    for (int c = 1; c <= turns; ++c) {
+#pragma unroll
+      for (int q = 0; q < NBUF; ++q) {
+#pragma unroll
+        for (int s = 0; s < KU; ++s)
+#pragma unroll
+          for (int i = 0; i < BM; ++i)
+#pragma unroll
+            for (int j = 0; j < BN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[q][s][i], fb[q][s][j],
+                                                               acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load(q, KU * (NBUF * c + q));  // the same group of the next turn
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < 16 * H / NT; ++i) {
-    const int e = i * NT + tid;
-    const int r = r0 + e / H;
-    const int64_t c = c0 + 2 * (e % H);
-    v[i].x = (r < K && c < N) ? Ut[(int64_t)r * ldu + c] : 0.0;
-    v[i].y = (r < K && c + 1 < N) ? Ut[(int64_t)r * ldu + c + 1] : 0.0;
   }
 }
 
-template <int NT, int LD, int W = 128>
-__device__ inline void store_stage(double (*X)[LD], const double2 v[16 * W / 2 / NT]) {
-  constexpr int H = W / 2;
-  const int tid = threadIdx.x;
+// P -= V V^T on the wave's block at (i0, j0), lower part, written to both
+// triangles. P's values are loaded before the products (they wait in
+// registers), so no load follows a store it might alias. The mirrored half
+// goes through the wave's own LDS strip, 16 columns at a time, and out as
+// whole row runs of 16 BM doubles instead of 32-byte pieces of 16 rows.
+template <int BM, int BN>
+__device__ __forceinline__ void direct_syrk(double* __restrict__ P, int64_t ldp, int64_t N,
+                                            const double* __restrict__ Ut, int64_t ldu, int32_t K,
+                                            int64_t i0, int64_t j0,
+                                            double (*strip)[16 * BM + 1]) {
+  const int lane = threadIdx.x & 63, li = lane & 15, kq = lane >> 4;
+  auto lower = [&](int i, int j, int v, int64_t* gi, int64_t* gj) {
+    *gi = i0 + 16 * i + 4 * v + kq;
+    *gj = j0 + 16 * j + li;
+    return *gi < N && *gj <= *gi;
+  };
+  double pv[BM][BN][4];
 #pragma unroll
-  for (int i = 0; i < 16 * H / NT; ++i) {
-    const int e = i * NT + tid;
-    *reinterpret_cast<double2*>(&X[e / H][2 * (e % H)]) = v[i];
-  }
-}
-
-// 128x128 tile per workgroup of 8 waves (4 x 2, each 32 x 64 = 2 x 4 MFMA
-// blocks), two workgroups per CU: four waves per SIMD hide the LDS and
-// barrier latency of each 16-deep stage.
-constexpr int SYRK_NT = 512;
-
-__device__ __forceinline__ void syrk_f64_body(double* __restrict__ P, int64_t ldp, int64_t N,
-    const double* __restrict__ Ut, int64_t ldu, int32_t K, int64_t T, int64_t per_xcd,
-    const int32_t* __restrict__ flags, int part, const int32_t* __restrict__ status, int64_t seq,
-    int64_t bid) {
-  if (seq_skip(status, seq)) return;
-  const int64_t t = xcd_tile(bid, per_xcd);
-  if (t >= T) return;
-  int I, J;
-  tile_of_blocked(t, (int)((N + ST - 1) / ST), &I, &J);
-  if (!tile_in_part(flags, part, I, J)) return;
-  const int64_t I0 = (int64_t)I * ST, J0 = (int64_t)J * ST;
-  __shared__ double As[2][SKC][SLD];
-  __shared__ double Bs[2][SKC][SLD];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;  // rows wm*32.., columns wn*64..
-  v4d acc[2][4];
+  for (int i = 0; i < BM; ++i)
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
-  const int nch = (K + SKC - 1) / SKC;
-  double2 ra[1024 / SYRK_NT], rb[1024 / SYRK_NT];
-  load_stage<SYRK_NT>(Ut, ldu, N, 0, K, I0, ra);
-  load_stage<SYRK_NT>(Ut, ldu, N, 0, K, J0, rb);
-  store_stage<SYRK_NT, SLD>(As[0], ra);
-  store_stage<SYRK_NT, SLD>(Bs[0], rb);
-  __syncthreads();
-  for (int ch = 0; ch < nch; ++ch) {
-    const int buf = ch & 1;
-    if (ch + 1 < nch) {
-      load_stage<SYRK_NT>(Ut, ldu, N, (ch + 1) * SKC, K, I0, ra);
-      load_stage<SYRK_NT>(Ut, ldu, N, (ch + 1) * SKC, K, J0, rb);
-    }
-#pragma unroll
-    for (int kk = 0; kk < SKC; kk += 4) {
-      const int kr = kk + (lane >> 4);
-      double a[2], b[4];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) a[q] = As[buf][kr][wm * 32 + q * 16 + (lane & 15)];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) b[q] = Bs[buf][kr][wn * 64 + q * 16 + (lane & 15)];
-#pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
-          acc[mi][ni] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
-    }
-    if (ch + 1 < nch) {
-      store_stage<SYRK_NT, SLD>(As[buf ^ 1], ra);
-      store_stage<SYRK_NT, SLD>(Bs[buf ^ 1], rb);
-    }
-    __syncthreads();
-  }
-  // epilogue: P[gi][gj] -= C (lower tiles; diagonal tiles keep gi >= gj so
-  // each element is written once), then the mirror P[gj][gi]. The mirror
-  // goes through LDS (the stage buffer, free now) 32 columns at a time, so
-  // each of its rows is written as one coalesced 1 KB run rather than in
-  // 32-byte pieces of 16 rows per store instruction.
-  const bool diag = (I == J);
-#pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < 4; ++ni)
+    for (int j = 0; j < BN; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int64_t gi = I0 + wm * 32 + mi * 16 + 4 * v + (lane >> 4);
-        const int64_t gj = J0 + wn * 64 + ni * 16 + (lane & 15);
-        if (gi < N && gj < N && (!diag || gi >= gj)) {
-          const double nv = P[gi * ldp + gj] - acc[mi][ni][v];
-          P[gi * ldp + gj] = nv;
-          acc[mi][ni][v] = nv;
-        }
+        int64_t gi, gj;
+        pv[i][j][v] = lower(i, j, v, &gi, &gj) ? P[gi * ldp + gj] : 0.0;
       }
-  constexpr int MP = ST + 1;  // pitch of the transposed chunk (doubles)
-  static_assert(32 * MP <= 2 * SKC * SLD, "a 32-column chunk fits the stage buffer");
-  double (*Tm)[MP] = reinterpret_cast<double (*)[MP]>(&As[0][0][0]);
+  v4d acc[BM][BN];
+  direct_product<BM, BN>(Ut, ldu, N, i0, Ut, ldu, N, j0, K, acc);
 #pragma unroll
-  for (int q = 0; q < ST / 32; ++q) {
-    if (wn == q / 2) {
+  for (int j = 0; j < BN; ++j) {
 #pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
+    for (int i = 0; i < BM; ++i)
 #pragma unroll
-        for (int nn = 0; nn < 2; ++nn)
+      for (int v = 0; v < 4; ++v) {
+        int64_t gi, gj;
+        const double nv = pv[i][j][v] - acc[i][j][v];
+        if (lower(i, j, v, &gi, &gj)) P[gi * ldp + gj] = nv;
+        strip[li][16 * i + 4 * v + kq] = nv;
+      }
+    __builtin_amdgcn_wave_barrier();  // the strip is one wave's: order only
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int ni = 2 * (q % 2) + nn;
-            const int c = ni * 16 + (lane & 15) - 32 * (q % 2);  // column in the chunk
-            const int r = wm * 32 + mi * 16 + 4 * v + (lane >> 4);
-            Tm[c][r] = acc[mi][ni][v];
-          }
+    for (int s = 0; s < 4 * BM; ++s) {
+      const int e = lane + 64 * s, c = e / (16 * BM), r = e % (16 * BM);
+      const int64_t gr = j0 + 16 * j + c, gc = i0 + r;  // mirror of (gc, gr)
+      if (gc < N && gr < gc) P[gr * ldp + gc] = strip[c][r];
     }
-    __syncthreads();
-    for (int e = tid; e < 32 * ST; e += SYRK_NT) {
-      const int c = e / ST, r = e % ST;
-      const int64_t gr = J0 + 32 * q + c, gc = I0 + r;  // mirror of (gc, gr)
-      if (gr < N && gc < N && (!diag || gc > gr)) P[gr * ldp + gc] = Tm[c][r];
-    }
-    __syncthreads();  // the chunk is read before the next one is written
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
-__global__ void __launch_bounds__(SYRK_NT, 2) k_syrk_f64(double* __restrict__ P, int64_t ldp,
-    int64_t N, const double* __restrict__ Ut, int64_t ldu, int32_t K, int64_t T, int64_t per_xcd,
-    const int32_t* __restrict__ flags, int part, const int32_t* __restrict__ status, int64_t seq) {
-  syrk_f64_body(P, ldp, N, Ut, ldu, K, T, per_xcd, flags, part, status, seq, blockIdx.x);
-}
-
-// Tail of the FP64 product. A launch of 128x128 tiles runs in rounds of
-// (workgroups per CU x CUs per XCD) tiles per XCD; the tiles past the last
-// full round would leave most CUs idle while they finish. They are computed
-// instead as 32x64 sub-tiles by this kernel, eight per tile (six on the
-// diagonal: the two above it are mirrors), each on 8 waves of 16 x 16 (one
-// MFMA block): many short workgroups spread the leftover work over the
-// chip and keep several waves per SIMD to hide the short stages' loads.
-// Every element accumulates the same MFMAs over k in the same order as in
-// the 128x128 kernel, so the result is bit for bit the same. Local tiles
-// main_per_xcd .. per_xcd - 1 of each XCD.
-constexpr int SUB_M = 32;
-constexpr int SUB_N = 64;
-constexpr int SUB_NT = 512;
-constexpr int SUB_PER_TILE = (ST / SUB_M) * (ST / SUB_N);
-
-__device__ __forceinline__ void syrk_f64_tail_body(double* __restrict__ P, int64_t ldp, int64_t N,
+// Tiles of 128x128 (tile_of_blocked, XCD-blocked), each as 128 / TM x 128 / TN
+// workgroups of 2 x 2 waves (TM = 32 BM, TN = 32 BN): SYRK_MAIN_WG = 2 of
+// 64x32 blocks, SYRK_SUB_PER_TILE = 4 of 32x32. Workgroup bid of the run of
+// local tiles [first, last) of each XCD.
+template <int BM, int BN>
+__device__ __forceinline__ void syrk_f64_body(double* __restrict__ P, int64_t ldp, int64_t N,
     const double* __restrict__ Ut, int64_t ldu, int32_t K, int64_t T, int64_t per_xcd,
-    int64_t main_per_xcd, const int32_t* __restrict__ flags, int part,
+    int64_t first, int64_t last, const int32_t* __restrict__ flags, int part,
     const int32_t* __restrict__ status, int64_t seq, int64_t bid) {
   if (seq_skip(status, seq)) return;
-  const int64_t local = main_per_xcd + (bid >> 3) / SUB_PER_TILE;
-  const int sub = (int)((bid >> 3) % SUB_PER_TILE);
-  const int si = sub / (ST / SUB_N), sj = sub % (ST / SUB_N);
-  if (local >= per_xcd) return;
+  constexpr int TM = 32 * BM, TN = 32 * BN, SJ = ST / TN, WG = ST / TM * SJ;
+  const int64_t local = first + (bid >> 3) / WG;
+  const int sub = (int)((bid >> 3) % WG);
+  if (local >= last) return;
   const int64_t t = (bid & 7) * per_xcd + local;
   if (t >= T) return;
   int I, J;
   tile_of_blocked(t, (int)((N + ST - 1) / ST), &I, &J);
   if (!tile_in_part(flags, part, I, J)) return;
-  if (I == J && si * SUB_M + SUB_M - 1 < sj * SUB_N) return;  // above the diagonal
-  const int64_t I0 = (int64_t)I * ST + si * SUB_M, J0 = (int64_t)J * ST + sj * SUB_N;
-  if (I0 >= N || J0 >= N) return;
-  __shared__ double As[2][SKC][SUB_M + 8];
-  __shared__ double Bs[2][SKC][SUB_N + 8];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 2, wn = wave & 3;  // rows wm*16.., columns wn*16..
-  v4d acc = (v4d){0.0, 0.0, 0.0, 0.0};
-  const int nch = (K + SKC - 1) / SKC;
-  // a stage: the 16 x 32 slice of the row panel (threads 0-255, one double2
-  // each) and the 16 x 64 slice of the column panel (all 512 threads)
-  constexpr int NA = SUB_NT / 2;
-  double2 ra[1], rb[1];
-  if (tid < NA) load_stage<NA, SUB_M>(Ut, ldu, N, 0, K, I0, ra);
-  load_stage<SUB_NT, SUB_N>(Ut, ldu, N, 0, K, J0, rb);
-  if (tid < NA) store_stage<NA, SUB_M + 8, SUB_M>(As[0], ra);
-  store_stage<SUB_NT, SUB_N + 8, SUB_N>(Bs[0], rb);
-  __syncthreads();
-  for (int ch = 0; ch < nch; ++ch) {
-    const int buf = ch & 1;
-    if (ch + 1 < nch) {
-      if (tid < NA) load_stage<NA, SUB_M>(Ut, ldu, N, (ch + 1) * SKC, K, I0, ra);
-      load_stage<SUB_NT, SUB_N>(Ut, ldu, N, (ch + 1) * SKC, K, J0, rb);
-    }
-#pragma unroll
-    for (int kk = 0; kk < SKC; kk += 4) {
-      const int kr = kk + (lane >> 4);
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(As[buf][kr][wm * 16 + (lane & 15)],
-                                                 Bs[buf][kr][wn * 16 + (lane & 15)], acc, 0,
-                                                 0, 0);
-    }
-    if (ch + 1 < nch) {
-      if (tid < NA) store_stage<NA, SUB_M + 8, SUB_M>(As[buf ^ 1], ra);
-      store_stage<SUB_NT, SUB_N + 8, SUB_N>(Bs[buf ^ 1], rb);
-    }
-    __syncthreads();
-  }
-  const bool diag = (I == J);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int64_t gi = I0 + wm * 16 + 4 * v + (lane >> 4);
-    const int64_t gj = J0 + wn * 16 + (lane & 15);
-    if (gi < N && gj < N && (!diag || gi >= gj)) {
-      const double nv = P[gi * ldp + gj] - acc[v];
-      P[gi * ldp + gj] = nv;
-      if (gi != gj) P[gj * ldp + gi] = nv;
-    }
-  }
+  __shared__ double strip[4][16][16 * BM + 1];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i0 = (int64_t)I * ST + sub / SJ * TM + (wave >> 1) * 16 * BM;
+  const int64_t j0 = (int64_t)J * ST + sub % SJ * TN + (wave & 1) * 16 * BN;
+  if (i0 >= N || j0 >= N || i0 + 16 * BM - 1 < j0) return;  // outside or above the diagonal
+  direct_syrk<BM, BN>(P, ldp, N, Ut, ldu, K, i0, j0, strip[wave]);
 }
 
-__global__ void __launch_bounds__(SUB_NT) k_syrk_f64_tail(double* __restrict__ P, int64_t ldp,
+// Main part: whole rounds of tiles in blocks of 64x32, two waves per SIMD.
+__global__ void __launch_bounds__(256, 2) k_syrk_f64(double* __restrict__ P, int64_t ldp,
     int64_t N, const double* __restrict__ Ut, int64_t ldu, int32_t K, int64_t T, int64_t per_xcd,
     int64_t main_per_xcd, const int32_t* __restrict__ flags, int part,
     const int32_t* __restrict__ status, int64_t seq) {
-  syrk_f64_tail_body(P, ldp, N, Ut, ldu, K, T, per_xcd, main_per_xcd, flags, part, status, seq,
-    blockIdx.x);
+  syrk_f64_body<4, 2>(P, ldp, N, Ut, ldu, K, T, per_xcd, 0, main_per_xcd, flags, part, status,
+                      seq, blockIdx.x);
+}
+
+// Tail: the tiles past the last whole round, in blocks of 32x32, which spread
+// the leftover work over the chip.
+__global__ void __launch_bounds__(256, 3) k_syrk_f64_tail(double* __restrict__ P, int64_t ldp,
+    int64_t N, const double* __restrict__ Ut, int64_t ldu, int32_t K, int64_t T, int64_t per_xcd,
+    int64_t main_per_xcd, const int32_t* __restrict__ flags, int part,
+    const int32_t* __restrict__ status, int64_t seq) {
+  syrk_f64_body<2, 2>(P, ldp, N, Ut, ldu, K, T, per_xcd, main_per_xcd, per_xcd, flags, part,
+                      status, seq, blockIdx.x);
+}
+
+// Small products: lower 32x32 tiles in row order, one workgroup of four 16x16
+// blocks each.
+__global__ void __launch_bounds__(256) k_syrk_f64_small(double* __restrict__ P, int64_t ldp,
+    int64_t N, const double* __restrict__ Ut, int64_t ldu, int32_t K,
+    const int32_t* __restrict__ flags, int part, const int32_t* __restrict__ status,
+    int64_t seq) {
+  if (seq_skip(status, seq)) return;
+  int I, J;
+  tile_of(blockIdx.x, &I, &J);
+  if (!tile_in_part(flags, part, I / (ST / 32), J / (ST / 32))) return;
+  __shared__ double strip[4][16][17];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i0 = (int64_t)I * 32 + (wave >> 1) * 16, j0 = (int64_t)J * 32 + (wave & 1) * 16;
+  if (i0 >= N || j0 >= N || i0 < j0) return;
+  direct_syrk<1, 1>(P, ldp, N, Ut, ldu, K, i0, j0, strip[wave]);
 }
 
 // Triangular solve of the update as one product: V^T = X U^T with
 // X = L^{-1} (block lower triangular, held transposed in LiT[k][row],
 // leading dimension n, zero above its diagonal blocks) and U^T (n x ncols,
-// leading dimension ldu). Same 128x128 tile, stage loader and MFMA layout
-// as k_syrk_f64; the k-range of row block I stops at its last row
-// ((I + 1) * 128), where X is zero beyond. Heavier row blocks are issued
-// first.
-// UPPER: X upper triangular instead (the operand holds X transposed all
-// the same), the k-range of row block I starting at its first row.
-template <bool UPPER>
+// leading dimension ldu), in the same blocks; the k-range of a block stops at
+// its own last row, where X is zero beyond. Longer k-ranges are issued first.
+// UPPER: X upper triangular instead (the operand holds X transposed all the
+// same), the k-range of a block starting at its first row.
+template <bool UPPER, int BM, int BN>
 __device__ __forceinline__ void linv_apply_body(const double* __restrict__ LiT,
     int32_t n, const double* __restrict__ Ut, int64_t ldu, int64_t ncols, double* __restrict__ Vt,
     int32_t nJ, const int32_t* __restrict__ status, int64_t seq) {
   if (seq_skip(status, seq)) return;
-  const int nI = (n + ST - 1) / ST;
+  constexpr int TM = 32 * BM, TN = 32 * BN;
+  const int nI = (n + TM - 1) / TM;
   const int I = UPPER ? (int)(blockIdx.x / nJ) : nI - 1 - (int)(blockIdx.x / nJ);
   const int J = (int)(blockIdx.x % nJ);
-  const int64_t I0 = (int64_t)I * ST, J0 = (int64_t)J * ST;
-  const int kb = UPPER ? I * ST : 0;  // first k of the row block (a multiple of SKC)
-  const int K = UPPER ? n : min(n, (I + 1) * ST);
-  __shared__ double As[2][SKC][SLD];
-  __shared__ double Bs[2][SKC][SLD];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  v4d acc[2][4];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int64_t i0 = (int64_t)I * TM + (wave >> 1) * 16 * BM;
+  const int64_t j0 = (int64_t)J * TN + (wave & 1) * 16 * BN;
+  if (i0 >= n || j0 >= ncols) return;
+  const int kb = UPPER ? (int)i0 : 0;
+  const int K = UPPER ? n - kb : min(n, (int)i0 + 16 * BM);
+  v4d acc[BM][BN];
+  direct_product<BM, BN>(LiT + (int64_t)kb * n, n, n, i0, Ut + kb * ldu, ldu, ncols, j0, K, acc);
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int i = 0; i < BM; ++i)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
-  const int nch = (K - kb + SKC - 1) / SKC;
-  double2 ra[1024 / SYRK_NT], rb[1024 / SYRK_NT];
-  load_stage<SYRK_NT>(LiT, n, n, kb, K, I0, ra);
-  load_stage<SYRK_NT>(Ut, ldu, ncols, kb, K, J0, rb);
-  store_stage<SYRK_NT, SLD>(As[0], ra);
-  store_stage<SYRK_NT, SLD>(Bs[0], rb);
-  __syncthreads();
-  for (int ch = 0; ch < nch; ++ch) {
-    const int buf = ch & 1;
-    if (ch + 1 < nch) {
-      load_stage<SYRK_NT>(LiT, n, n, kb + (ch + 1) * SKC, K, I0, ra);
-      load_stage<SYRK_NT>(Ut, ldu, ncols, kb + (ch + 1) * SKC, K, J0, rb);
-    }
-#pragma unroll
-    for (int kk = 0; kk < SKC; kk += 4) {
-      const int kr = kk + (lane >> 4);
-      double a[2], b[4];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) a[q] = As[buf][kr][wm * 32 + q * 16 + (lane & 15)];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) b[q] = Bs[buf][kr][wn * 64 + q * 16 + (lane & 15)];
-#pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
-          acc[mi][ni] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
-    }
-    if (ch + 1 < nch) {
-      store_stage<SYRK_NT, SLD>(As[buf ^ 1], ra);
-      store_stage<SYRK_NT, SLD>(Bs[buf ^ 1], rb);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < 4; ++ni)
+    for (int j = 0; j < BN; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int64_t gi = I0 + wm * 32 + mi * 16 + 4 * v + (lane >> 4);
-        const int64_t gj = J0 + wn * 64 + ni * 16 + (lane & 15);
-        if (gi < n && gj < ncols) Vt[gi * ldu + gj] = acc[mi][ni][v];
+        const int64_t gi = i0 + 16 * i + 4 * v + (lane >> 4);
+        const int64_t gj = j0 + 16 * j + (lane & 15);
+        if (gi < n && gj < ncols) Vt[gi * ldu + gj] = acc[i][j][v];
       }
 }
 
-template <bool UPPER>
-__global__ void __launch_bounds__(SYRK_NT, 2) k_linv_apply(const double* __restrict__ LiT,
+template <bool UPPER, int BM, int BN>
+__global__ void __launch_bounds__(256, 2) k_linv_apply(const double* __restrict__ LiT,
     int32_t n, const double* __restrict__ Ut, int64_t ldu, int64_t ncols, double* __restrict__ Vt,
     int32_t nJ, const int32_t* __restrict__ status, int64_t seq) {
-  linv_apply_body<UPPER>(LiT, n, Ut, ldu, ncols, Vt, nJ, status, seq);
+  linv_apply_body<UPPER, BM, BN>(LiT, n, Ut, ldu, ncols, Vt, nJ, status, seq);
 }
 
 // ------------------------------------------------ low-precision operands
@@ -744,16 +677,28 @@ __global__ void __launch_bounds__(SYRK_NT, 2) k_syrk_bf16x3(double* __restrict__
   syrk_bf16x3_body(P, ldp, N, Vhi, Vlo, Kp, T, per_xcd, flags, part, status, seq, blockIdx.x);
 }
 
-static_assert(SUB_PER_TILE == SYRK_SUB_PER_TILE, "sub-tiles per tile");
+static_assert(ST / 128 * (ST / 64) == SYRK_MAIN_WG && ST / 64 * (ST / 64) == SYRK_SUB_PER_TILE,
+              "workgroups per tile");
 
+// Whole rounds of tiles per XCD go to the main part: two workgroups (of four
+// waves) fit a CU, two make a tile, so a round is one tile per CU. A last
+// round that is at least three quarters full is counted as whole.
 void syrk_tiles(int64_t N, int32_t cu_count, int64_t* T, int64_t* per_xcd,
                 int64_t* main_per_xcd) {
   const int64_t nt = ceil_div(N, ST);
   *T = nt * (nt + 1) / 2;
   *per_xcd = ceil_div(*T, 8);
-  // whole rounds of 128x128 tiles per XCD, the rest as 32x64 sub-tiles
-  const int64_t slots = cu_count > 0 ? (int64_t)cu_count / 8 * 2 : 64;
-  *main_per_xcd = slots > 0 ? *per_xcd / slots * slots : *per_xcd;
+  const int64_t slots = cu_count > 0 ? cu_count / 8 : 32;
+  *main_per_xcd = slots > 0 ? (*per_xcd + slots / 4) / slots * slots : *per_xcd;
+  if (*main_per_xcd > *per_xcd) *main_per_xcd = *per_xcd;
+}
+
+// Products whose blocks of 32x32 would leave most SIMDs without a wave take
+// blocks of 16x16: at K = 1024, N = 800 (350 lower blocks of 32x32) 38 us
+// against 49, N = 1100 (650) 55 against 51.
+static bool syrk_is_small(int64_t N, int32_t cu_count) {
+  const int64_t nb = ceil_div(N, 32);
+  return nb * (nb + 1) / 2 < 2 * (int64_t)(cu_count > 0 ? cu_count : 256);
 }
 
 rbf_status syrk_update(rbf_ctx* ctx, double* P, int64_t ldp, int64_t N, const double* Ut,
@@ -766,16 +711,24 @@ rbf_status syrk_update(rbf_ctx* ctx, double* P, int64_t ldp, int64_t N, const do
   rbf_status st;
   if (prec == RBF_F64) {
     prof_begin(ctx, RBF_PROF_SYRK);
+    if (syrk_is_small(N, ctx->cu_count)) {
+      const int64_t nb = ceil_div(N, 32);
+      k_syrk_f64_small<<<(unsigned)(nb * (nb + 1) / 2), 256, 0, ctx->stream>>>(
+          P, ldp, N, Ut, ldu, Bc, flags, part, ctx->d_status, seq);
+      RBF_LAUNCHED(ctx, "k_syrk_f64_small");
+      prof_end(ctx, RBF_PROF_SYRK);
+      return RBF_OK;
+    }
     if (main_per_xcd > 0) {
-      k_syrk_f64<<<(unsigned)(main_per_xcd * 8), SYRK_NT, 0, ctx->stream>>>(
-          P, ldp, N, Ut, ldu, Bc, T, per_xcd, flags, part, ctx->d_status, seq);
+      k_syrk_f64<<<(unsigned)(main_per_xcd * 8 * SYRK_MAIN_WG), 256, 0, ctx->stream>>>(
+          P, ldp, N, Ut, ldu, Bc, T, per_xcd, main_per_xcd, flags, part, ctx->d_status, seq);
       RBF_LAUNCHED(ctx, "k_syrk_f64");
     }
     if (main_per_xcd < per_xcd) {
-      const unsigned gt = (unsigned)((per_xcd - main_per_xcd) * 8 * SUB_PER_TILE);
-      k_syrk_f64_tail<<<gt, SUB_NT, 0, ctx->stream>>>(P, ldp, N, Ut, ldu, Bc, T, per_xcd,
-                                                      main_per_xcd, flags, part, ctx->d_status,
-                                                      seq);
+      const unsigned gt = (unsigned)((per_xcd - main_per_xcd) * 8 * SYRK_SUB_PER_TILE);
+      k_syrk_f64_tail<<<gt, 256, 0, ctx->stream>>>(P, ldp, N, Ut, ldu, Bc, T, per_xcd,
+                                                   main_per_xcd, flags, part, ctx->d_status,
+                                                   seq);
       RBF_LAUNCHED(ctx, "k_syrk_f64_tail");
     }
     prof_end(ctx, RBF_PROF_SYRK);
@@ -818,24 +771,24 @@ rbf_status syrk_update(rbf_ctx* ctx, double* P, int64_t ldp, int64_t N, const do
 // Covariance products of a round's jobs, each workgroup finding its job
 // from the prefix of per-job workgroup counts (multiples of 8, so a job's
 // local workgroup index keeps the XCD of the global one).
-__global__ void __launch_bounds__(SYRK_NT, 2) k_syrk_f64_g(const GJob* __restrict__ jobs,
-                                                           const int64_t* __restrict__ pre,
-                                                           int32_t n) {
+__global__ void __launch_bounds__(256, 2) k_syrk_f64_g(const GJob* __restrict__ jobs,
+                                                       const int64_t* __restrict__ pre,
+                                                       int32_t n) {
   const int64_t b = blockIdx.x;
   const int32_t j = job_of(pre, n, b);
   const GJob& J = jobs[j];
-  syrk_f64_body(J.P, J.ldp, J.N, J.Vt, J.ldu, J.Bc, J.T, J.per_xcd, nullptr, 0, J.status,
-                J.seq, b - pre[j]);
+  syrk_f64_body<4, 2>(J.P, J.ldp, J.N, J.Vt, J.ldu, J.Bc, J.T, J.per_xcd, 0, J.main_per_xcd,
+                      nullptr, 0, J.status, J.seq, b - pre[j]);
 }
 
-__global__ void __launch_bounds__(SUB_NT) k_syrk_f64_tail_g(const GJob* __restrict__ jobs,
+__global__ void __launch_bounds__(256, 3) k_syrk_f64_tail_g(const GJob* __restrict__ jobs,
                                                             const int64_t* __restrict__ pre,
                                                             int32_t n) {
   const int64_t b = blockIdx.x;
   const int32_t j = job_of(pre, n, b);
   const GJob& J = jobs[j];
-  syrk_f64_tail_body(J.P, J.ldp, J.N, J.Vt, J.ldu, J.Bc, J.T, J.per_xcd, J.main_per_xcd,
-                     nullptr, 0, J.status, J.seq, b - pre[j]);
+  syrk_f64_body<2, 2>(J.P, J.ldp, J.N, J.Vt, J.ldu, J.Bc, J.T, J.per_xcd, J.main_per_xcd,
+                      J.per_xcd, nullptr, 0, J.status, J.seq, b - pre[j]);
 }
 
 __global__ void __launch_bounds__(256) k_cvt_f32_g(const GJob* __restrict__ jobs) {
@@ -875,12 +828,11 @@ rbf_status syrk_grouped(rbf_ctx* ctx, const GRound& r, rbf_prec prec) {
   if (r.n <= 0) return RBF_OK;
   if (prec == RBF_F64) {
     if (r.n_main > 0) {
-      k_syrk_f64_g<<<(unsigned)r.n_main, SYRK_NT, 0, ctx->stream>>>(r.jobs, r.pre_main, r.n);
+      k_syrk_f64_g<<<(unsigned)r.n_main, 256, 0, ctx->stream>>>(r.jobs, r.pre_main, r.n);
       RBF_LAUNCHED(ctx, "k_syrk_f64_g");
     }
     if (r.n_tail > 0) {
-      k_syrk_f64_tail_g<<<(unsigned)r.n_tail, SUB_NT, 0, ctx->stream>>>(r.jobs, r.pre_tail,
-                                                                        r.n);
+      k_syrk_f64_tail_g<<<(unsigned)r.n_tail, 256, 0, ctx->stream>>>(r.jobs, r.pre_tail, r.n);
       RBF_LAUNCHED(ctx, "k_syrk_f64_tail_g");
     }
     return RBF_OK;
@@ -902,27 +854,52 @@ rbf_status syrk_grouped(rbf_ctx* ctx, const GRound& r, rbf_prec prec) {
   return RBF_OK;
 }
 
-// Grouped V^T = L^{-1} U^T (one launch over the round's jobs).
-__global__ void __launch_bounds__(SYRK_NT, 2) k_linv_apply_g(const GJob* __restrict__ jobs) {
+// Grouped V^T = L^{-1} U^T (one launch over the round's jobs, blocks of
+// 32x32: a round's jobs fill the chip together).
+__global__ void __launch_bounds__(256, 2) k_linv_apply_g(const GJob* __restrict__ jobs) {
   const GJob& J = jobs[blockIdx.z];
-  const int32_t nI = (J.Bp + ST - 1) / ST, nJ = (int32_t)((J.ncols + ST - 1) / ST);
+  const int32_t nI = (J.Bp + LINV_TILE - 1) / LINV_TILE;
+  const int32_t nJ = (int32_t)((J.ncols + LINV_TILE - 1) / LINV_TILE);
   if ((int32_t)blockIdx.x >= nI * nJ) return;
-  linv_apply_body<false>(J.LiT, J.Bp, J.Ut, J.ldu, J.ncols, J.Vt, nJ, J.status, J.seq);
+  linv_apply_body<false, LINV_TILE / 32, LINV_TILE / 32>(J.LiT, J.Bp, J.Ut, J.ldu, J.ncols, J.Vt,
+                                                         nJ, J.status, J.seq);
 }
 
 rbf_status linv_apply_grouped(rbf_ctx* ctx, const GRound& r) {
   if (r.n <= 0 || r.la_x <= 0) return RBF_OK;
-  k_linv_apply_g<<<dim3((unsigned)r.la_x, 1, (unsigned)r.n), SYRK_NT, 0, ctx->stream>>>(r.jobs);
+  k_linv_apply_g<<<dim3((unsigned)r.la_x, 1, (unsigned)r.n), 256, 0, ctx->stream>>>(r.jobs);
   RBF_LAUNCHED(ctx, "k_linv_apply_g");
   return RBF_OK;
 }
 
-rbf_status linv_apply(rbf_ctx* ctx, const double* LiT, int32_t n, const double* Ut,
-                      int64_t ldu, int64_t ncols, double* Vt, int64_t seq) {
-  if (n <= 0 || ncols <= 0) return RBF_OK;
-  const int64_t nI = ceil_div(n, ST), nJ = ceil_div(ncols, ST);
-  k_linv_apply<false><<<(unsigned)(nI * nJ), SYRK_NT, 0, ctx->stream>>>(
+template <bool UPPER, int BM, int BN>
+static void launch_linv(rbf_ctx* ctx, const double* LiT, int32_t n, const double* Ut, int64_t ldu,
+                        int64_t ncols, double* Vt, int64_t seq) {
+  const int64_t nI = ceil_div(n, 32 * BM), nJ = ceil_div(ncols, 32 * BN);
+  k_linv_apply<UPPER, BM, BN><<<(unsigned)(nI * nJ), 256, 0, ctx->stream>>>(
       LiT, n, Ut, ldu, ncols, Vt, (int32_t)nJ, ctx->d_status, seq);
+}
+
+// Block shape by the number of blocks against the chip's SIMDs (1024): the
+// launch ends with its longest block (n rows of products), so small ones take
+// 16x16 (n = 1024, 700 columns: 35 us against 44 in blocks of 32x32; 1000
+// columns: 44 against 44).
+rbf_status linv_apply(rbf_ctx* ctx, const double* LiT, int32_t n, const double* Ut,
+                      int64_t ldu, int64_t ncols, double* Vt, int64_t seq, bool upper) {
+  if (n <= 0 || ncols <= 0) return RBF_OK;
+  const int64_t simds = 4 * (int64_t)(ctx->cu_count > 0 ? ctx->cu_count : 256);
+  const bool small = ceil_div(n, 32) * ceil_div(ncols, 32) < simds;
+  if (upper) {
+    if (small)
+      launch_linv<true, 1, 1>(ctx, LiT, n, Ut, ldu, ncols, Vt, seq);
+    else
+      launch_linv<true, 2, 2>(ctx, LiT, n, Ut, ldu, ncols, Vt, seq);
+  } else {
+    if (small)
+      launch_linv<false, 1, 1>(ctx, LiT, n, Ut, ldu, ncols, Vt, seq);
+    else
+      launch_linv<false, 2, 2>(ctx, LiT, n, Ut, ldu, ncols, Vt, seq);
+  }
   RBF_LAUNCHED(ctx, "k_linv_apply");
   return RBF_OK;
 }
@@ -958,10 +935,7 @@ rbf_status syrk_update_joseph(rbf_ctx* ctx, double* P, int64_t ldp, int64_t N, c
   const dim3 gt((unsigned)ceil_div(Bpc, 32), (unsigned)ceil_div(Bpc, 32));
   k_transpose_f64<<<gt, 256, 0, ctx->stream>>>(LiT, Bpc, Lr, ctx->d_status, seq);
   RBF_LAUNCHED(ctx, "k_transpose_f64");
-  const int64_t nI = ceil_div(Bpc, ST), nJ = ceil_div(N, ST);
-  k_linv_apply<true><<<(unsigned)(nI * nJ), SYRK_NT, 0, ctx->stream>>>(
-      Lr, Bpc, Vt, ldu, N, Kt, (int32_t)nJ, ctx->d_status, seq);
-  RBF_LAUNCHED(ctx, "k_linv_apply");
+  RBF_TRY(linv_apply(ctx, Lr, Bpc, Vt, ldu, N, Kt, seq, true));
   const unsigned gc = (unsigned)ceil_div((int64_t)Bc * ldu, 256);
   k_cvt_f32<<<gc, 256, 0, ctx->stream>>>(Kt, ldu, Bc, N, X, ctx->d_status, seq);
   RBF_LAUNCHED(ctx, "k_cvt_f32");

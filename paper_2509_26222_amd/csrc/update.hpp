@@ -118,7 +118,7 @@ rbf_status chol_blocked(rbf_ctx* ctx, double* S, int32_t n, double* Lb, double* 
 // triangular solve as one product (FP64 in every form: the gain V feeds the
 // weight update w += V t directly).
 rbf_status linv_apply(rbf_ctx* ctx, const double* LiT, int32_t n, const double* Ut,
-                      int64_t ldu, int64_t ncols, double* Vt, int64_t seq);
+                      int64_t ldu, int64_t ncols, double* Vt, int64_t seq, bool upper = false);
 
 // X := L^{-1} X (trans = false) or X := L^{-T} X (trans = true) in place for
 // X with nblk*64 rows, ncols columns and leading dimension ldx, with L given
@@ -256,12 +256,15 @@ rbf_status syrk_grouped(rbf_ctx* ctx, const GRound& r, rbf_prec prec);
 rbf_status linv_apply_grouped(rbf_ctx* ctx, const GRound& r);
 
 // Covariance product tiles of N rows: T lower 128x128 tiles, per_xcd of
-// them per XCD, main_per_xcd of those computed whole and the rest as
-// 32x64 sub-tiles (the single-call rule: whole rounds of two workgroups per
-// CU as 128x128 tiles).
+// them per XCD, main_per_xcd of those in blocks of 64x32 per wave and the
+// rest in blocks of 32x32 (the single-call rule), with the workgroups that
+// one tile takes in either form; the FP32 and BF16 products take one.
 void syrk_tiles(int64_t N, int32_t cu_count, int64_t* T, int64_t* per_xcd,
                 int64_t* main_per_xcd);
-constexpr int SYRK_SUB_PER_TILE = 8;
+constexpr int SYRK_MAIN_WG = 2;
+constexpr int SYRK_SUB_PER_TILE = 4;
+// Rows and columns of V^T per workgroup of the grouped gain product.
+constexpr int LINV_TILE = 64;
 
 // Sparse solve helpers (solve.hip): R (N x nrhs, leading dimension nrhs)
 // = B - calH X for calH in CSR; the 2-norms of the nrhs columns of A (N
