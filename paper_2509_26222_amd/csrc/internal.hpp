@@ -45,6 +45,7 @@ enum WsSlot {
   WS_SOLVE6,
   WS_SOLVE7,    // solve: L^{-1} of every diagonal block, transposed
   WS_SOLVE8,    // solve: one s x s block, and the second sweep vector
+  WS_GRAM,      // assembly: dense blocks of the points' bins
   WS_COUNT
 };
 
