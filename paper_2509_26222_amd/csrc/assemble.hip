@@ -522,8 +522,8 @@ rbf_status rbf_assemble_gram(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* 
   // blocks (the whole call) against 364 row-wise, 40,000 points 400 against
   // 630; 4,900 centers and 2,450 points 117 against 107.
   if (ld <= GRAM_RMAX && 4 * M >= 3 * N)
-    ws = (char*)ws_get(ctx, WS_GRAM, (size_t)(strip * blk), &st);
-  if (!ws) {  // or no memory for the blocks
+    ws = (char*)ws_try(ctx, WS_GRAM, (size_t)(strip * blk));
+  if (!ws) {  // or no room for the blocks
     k_gram_values<<<ceil_div(N, 4), 256, 0, ctx->stream>>>(
         g->d_cxy, g->d_rank, N, g->d_idx, pxy, pz, pstart, geom(g), k, rowptr, colidx, lambda,
         vals, b);

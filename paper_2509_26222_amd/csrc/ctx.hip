@@ -51,6 +51,19 @@ void* ws_get(rbf_ctx* ctx, int slot, size_t bytes, rbf_status* st) {
   return p;
 }
 
+void* ws_try(rbf_ctx* ctx, int slot, size_t bytes) {
+  if (ctx->ws_bytes[slot] < bytes) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    if (cap != hipStreamCaptureStatusNone) return nullptr;
+  }
+  rbf_status st;
+  return ws_get(ctx, slot, bytes, &st);
+}
+
 rbf_status check_launch(rbf_ctx* ctx, const char* what) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess)

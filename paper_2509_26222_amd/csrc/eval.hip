@@ -23,6 +23,7 @@
 // scaled by ks, so that phi = exp(-d'^2) (FP64) or exp2(-d'^2) (FP32,
 // v_exp_f32): per candidate two subtractions, the squared distance, the
 // exponential, the support test and three accumulations.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -658,23 +659,45 @@ __global__ void __launch_bounds__(GN_SUM_T) k_eval_gn_sum(const double* __restri
 }
 
 // Adjoint: L = sum_i gf_i f_i + gr_i r_i. With a_i = gf_i - gr_i:
-//   dL/dw_j   = sum_i a_i phi(xi_i, c_j)            (scattered, atomics)
+//   dL/dw_j   = sum_i a_i phi(xi_i, c_j)            (scattered)
 //   dL/dxi_i  = (a_i f_x, a_i f_y, gr_i),  dL/dp_i = R^T dL/dxi_i
 //   dL/dpose  = sum_i [p_i x (R^T dL/dxi_i), dL/dxi_i]  (block-reduced)
-template <typename T, bool POSE>
-__global__ void __launch_bounds__(256) k_eval_adjoint(
+//
+// dL/dw takes about 28 FP64 additions per point. PLANES: one workgroup per CU
+// takes a share of the points, adds in LDS (ds_add_f64) and leaves its N sums
+// in a plane of its own, which k_adjoint_sum adds up. Else every addition is a
+// device atomic, and these bound the kernel (5.6 million of them at 200,000
+// points). 200,000 FP64 points, 10,000 centers: 192 us with device atomics,
+// 40 + 7 us with planes, bound by the FP64 exponentials of the candidates.
+constexpr int64_t ADJ_PLANES = 256;            // one workgroup per CU
+constexpr int ADJ_NT = 1024;                   // its threads (four waves per SIMD)
+constexpr int64_t ADJ_LDS_N = 18 * 1024;       // 144 KB of sums
+constexpr int64_t ADJ_MIN_PLANES = 16;         // 256 points each
+
+template <typename T, bool POSE, bool PLANES>
+__global__ void __launch_bounds__(PLANES ? ADJ_NT : 256) k_eval_adjoint(
     const T* __restrict__ pts, int64_t Q, const typename Vec4<T>::type* __restrict__ tab0,
     int64_t N, const int32_t* __restrict__ estart, EGeom g, EvalK<T> k0,
     const double* __restrict__ dpose,
     const T* __restrict__ gbar_f, const T* __restrict__ gbar_r, T* __restrict__ d_pts,
     double* __restrict__ d_w, double* __restrict__ d_pose) {
-  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPP;
+  constexpr int NT = PLANES ? ADJ_NT : 256, PPB = NT / LPP;
+  extern __shared__ double hw[];  // PLANES: this workgroup's dL/dw
   const int part = threadIdx.x % LPP;
   EvalK<T> k = k0;
   if (POSE) load_pose(k, dpose);
   const TabReader<T> tab(tab0, N);
   double acc[6] = {0, 0, 0, 0, 0, 0};
-  if (i < Q) {  // the lanes of a quad share this branch
+  int64_t i = (int64_t)blockIdx.x * PPB + threadIdx.x / LPP, end = i + 1;
+  if (PLANES) {
+    const int64_t share = (Q + gridDim.x - 1) / gridDim.x;
+    i = blockIdx.x * share + threadIdx.x / LPP;
+    end = (blockIdx.x + 1) * share;
+    for (int e = threadIdx.x; e < N; e += NT) hw[e] = 0.0;
+    __syncthreads();
+  }
+  if (end > Q) end = Q;
+  for (; i < end; i += PPB) {  // the lanes of a quad share this loop
     T xr, yr, zw, px, py, pz;
     point_rel<T, POSE>(pts, i, k, xr, yr, zw, px, py, pz);
     const T gf = gbar_f ? gbar_f[i] : (T)0;
@@ -689,8 +712,12 @@ __global__ void __launch_bounds__(256) k_eval_adjoint(
                         const T we = c.z * e;
                         sx += we * dx;
                         sy += we * dy;
-                        if (scatter && e != (T)0)
-                          atomicAdd(&d_w[bits_idx(c.w)], (double)(a * e));
+                        if (scatter && e != (T)0) {
+                          if (PLANES)
+                            atomicAdd(&hw[bits_idx(c.w)], (double)(a * e));
+                          else
+                            atomicAdd(&d_w[bits_idx(c.w)], (double)(a * e));
+                        }
                       });
     sx = quad_sum(sx);
     sy = quad_sum(sy);
@@ -706,12 +733,12 @@ __global__ void __launch_bounds__(256) k_eval_adjoint(
           d_pts[3 * i + 1] = q1;
           d_pts[3 * i + 2] = q2;
         }
-        acc[0] = (double)(py * q2 - pz * q1);
-        acc[1] = (double)(pz * q0 - px * q2);
-        acc[2] = (double)(px * q1 - py * q0);
-        acc[3] = (double)dx0;
-        acc[4] = (double)dx1;
-        acc[5] = (double)dx2;
+        acc[0] += (double)(py * q2 - pz * q1);
+        acc[1] += (double)(pz * q0 - px * q2);
+        acc[2] += (double)(px * q1 - py * q0);
+        acc[3] += (double)dx0;
+        acc[4] += (double)dx1;
+        acc[5] += (double)dx2;
       }
     } else if (d_pts && part == 0) {
       d_pts[2 * i] = dx0;
@@ -719,7 +746,7 @@ __global__ void __launch_bounds__(256) k_eval_adjoint(
     }
   }
   if (POSE && d_pose) {
-    __shared__ double red[6][4];
+    __shared__ double red[6][NT / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
@@ -729,11 +756,32 @@ __global__ void __launch_bounds__(256) k_eval_adjoint(
     }
     __syncthreads();
     if (threadIdx.x < 6) {
-      double v = red[threadIdx.x][0] + red[threadIdx.x][1] + red[threadIdx.x][2] +
-                 red[threadIdx.x][3];
+      double v = red[threadIdx.x][0];
+      for (int q = 1; q < NT / 64; ++q) v += red[threadIdx.x][q];
       atomicAdd(&d_pose[threadIdx.x], v);
     }
   }
+  if (PLANES) {
+    __syncthreads();
+    for (int e = threadIdx.x; e < N; e += NT) d_w[blockIdx.x * N + e] = hw[e];
+  }
+}
+
+// d_w += the planes: 64 centers per workgroup, 16 waves over the planes.
+__global__ void __launch_bounds__(1024) k_adjoint_sum(const double* __restrict__ plane,
+                                                      int planes, int64_t N,
+                                                      double* __restrict__ d_w) {
+  __shared__ double s[16][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+  double v = 0.0;
+  if (e < N)
+    for (int q = w; q < planes; q += 16) v += plane[q * N + e];
+  s[w][lane] = v;
+  __syncthreads();
+  if (w != 0 || e >= N) return;
+  for (int q = 1; q < 16; ++q) v += s[q][lane];
+  if (v != 0.0) atomicAdd(&d_w[e], v);  // other calls may add to d_w at the same time
 }
 
 // ---- pose increments on SO(3) x R^3 (differentiation form)
@@ -1039,13 +1087,39 @@ static rbf_status adjoint_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g
   RBF_TRY(pack<T>(ctx, p, g, w, &tab));
   const EvalK<T> k = make_consts<T>(p, g, pose, 0.0);
   const EGeom eg = egeom(p, g);
+  // Planes when the sums fit the LDS and the points outweigh clearing, writing
+  // and adding up N sums per plane. Whole calls by planes and by atomics:
+  // N = 400, 2048 points 24 and 24 us, 8192 21 and 66; N = 10,000, 8192
+  // points 20 and 18, 20,000 22 and 27, 200,000 43 and 184; N = 17,956,
+  // 20,000 points 27 and 26, 50,000 34 and 51 (FP32).
+  // The buffer's size depends on N alone, so that it grows with the grid's
+  // size only, as the table's; not taken if it would grow during a capture.
+  const int64_t planes = std::min<int64_t>(ADJ_PLANES, Q / 256);
+  double* plane = nullptr;
+  if (d_w && g->N <= ADJ_LDS_N && planes >= ADJ_MIN_PLANES && Q >= 2 * g->N)
+    plane = (double*)ws_try(ctx, WS_ADJ, sizeof(double) * ADJ_PLANES * g->N);
+  if (plane) {
+    const size_t lds = sizeof(double) * (size_t)g->N;
+    if (dim == 3)
+      k_eval_adjoint<T, true, true><<<(unsigned)planes, ADJ_NT, lds, ctx->stream>>>(
+          (const T*)pts, Q, tab, g->N, g->d_estart, eg, k, dpose, (const T*)gf, (const T*)gr,
+          (T*)d_pts, plane, d_pose);
+    else
+      k_eval_adjoint<T, false, true><<<(unsigned)planes, ADJ_NT, lds, ctx->stream>>>(
+          (const T*)pts, Q, tab, g->N, g->d_estart, eg, k, nullptr, (const T*)gf, nullptr,
+          (T*)d_pts, plane, nullptr);
+    RBF_LAUNCHED(ctx, "k_eval_adjoint");
+    k_adjoint_sum<<<ceil_div(g->N, 64), 1024, 0, ctx->stream>>>(plane, (int)planes, g->N, d_w);
+    RBF_LAUNCHED(ctx, "k_adjoint_sum");
+    return RBF_OK;
+  }
   const unsigned blocks = (unsigned)ceil_div(Q * LPP, 256);
   if (dim == 3)
-    k_eval_adjoint<T, true><<<blocks, 256, 0, ctx->stream>>>(
+    k_eval_adjoint<T, true, false><<<blocks, 256, 0, ctx->stream>>>(
         (const T*)pts, Q, tab, g->N, g->d_estart, eg, k, dpose, (const T*)gf, (const T*)gr,
         (T*)d_pts, d_w, d_pose);
   else
-    k_eval_adjoint<T, false><<<blocks, 256, 0, ctx->stream>>>(
+    k_eval_adjoint<T, false, false><<<blocks, 256, 0, ctx->stream>>>(
         (const T*)pts, Q, tab, g->N, g->d_estart, eg, k, nullptr, (const T*)gf, nullptr, (T*)d_pts,
         d_w, nullptr);
   RBF_LAUNCHED(ctx, "k_eval_adjoint");

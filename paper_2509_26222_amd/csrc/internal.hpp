@@ -46,6 +46,7 @@ enum WsSlot {
   WS_SOLVE7,    // solve: L^{-1} of every diagonal block, transposed
   WS_SOLVE8,    // solve: one s x s block, and the second sweep vector
   WS_GRAM,      // assembly: dense blocks of the points' bins
+  WS_ADJ,       // adjoint: planes of dL/dw
   WS_COUNT
 };
 
@@ -143,6 +144,9 @@ namespace rbf {
 
 rbf_status fail(rbf_ctx* ctx, rbf_status s, const char* fmt, ...);
 void* ws_get(rbf_ctx* ctx, int slot, size_t bytes, rbf_status* st);
+// The same for a faster form that can be done without: null if the buffer would
+// have to grow while the stream captures, or cannot (no error is returned).
+void* ws_try(rbf_ctx* ctx, int slot, size_t bytes);
 rbf_status check_launch(rbf_ctx* ctx, const char* what);
 rbf_status set_device(rbf_ctx* ctx);
 
