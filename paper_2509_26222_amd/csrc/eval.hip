@@ -458,6 +458,110 @@ __device__ inline void sum_point_mesh(T xr, T yr, int part, const MeshReader<T>&
   sy = quad_sum(sy_);
 }
 
+// ---- mesh form with the node weights in LDS
+//
+// One workgroup per CU keeps the whole dense node array in LDS,
+// filled straight from the weights (no packing launch), and takes a share of
+// the points, one lane per point. The quad form forms a point's setup, pose
+// and outputs in four lanes and its window loads keep the L1 busy (a wave's 16
+// loads of a window touch 64 to 128 lines each); here a lane reads its window's
+// rows from LDS. Every sum is taken in the quad form's order (columns j,
+// j + 4, ... of lane j, then the butterfly), so the two forms agree bit for
+// bit. 5,000,000 FP32 points on 100 x 100 centers: 174 -> 85 us; 200,000: 9.7 +
+// 2.4 (packing) -> 11.2 us and a launch less. Bound by the FP32 VALU (about 600
+// instructions per wavefront of 64 points), at a scan's size by filling the LDS
+// and the launch.
+
+// Nodes of the dense array that one CU's LDS holds beside the reductions.
+constexpr int64_t MESH_LDS_BYTES = 152 * 1024;
+
+template <typename T>
+struct MeshTab {
+  const int32_t* map;  // center of each dense node, -1: none
+  const double* w;
+  int32_t n;           // dense nodes
+  MGeom<T> mg;
+};
+
+// Fill the LDS table. All loads of a step are issued before the first use.
+template <typename T>
+__device__ inline void fill_mesh(const MeshTab<T>& t, T* wt, int tid, int nt) {
+  constexpr int U = 16;
+  for (int e0 = tid; e0 < t.n; e0 += U * nt) {
+    int c[U];
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = t.map[min(e0 + u * nt, t.n - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = t.w[max(c[u], 0)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (e0 + u * nt < t.n) wt[e0 + u * nt] = c[u] >= 0 ? (T)v[u] : (T)0;
+  }
+}
+
+// f, sum w phi dx', sum w phi dy' of one lane's point.
+template <typename T, int MW>
+__device__ inline void sum_lane_mesh(T xr, T yr, const T* wt, const MGeom<T>& m,
+                                     const EvalK<T>& k, T& f, T& sx, T& sy) {
+  const float u = (float)(xr * m.inv_res), v = (float)(yr * m.inv_res);
+  const bool ok = fabsf(u) < 16777216.f && fabsf(v) < 16777216.f;  // also NaN
+  const int i0 = ok ? min(max((int)ceilf(u - m.rp), m.ilo), m.ihi) : m.ilo;
+  const int j0 = ok ? min(max((int)ceilf(v - m.rp), m.jlo), m.jhi) : m.jlo;
+  const T xs = ok ? xr * k.ks : (T)1e18, ys = ok ? yr * k.ks : (T)1e18;
+  T dx[MW], dx2[MW], cs[MW], cy[MW];
+#pragma unroll
+  for (int q = 0; q < MW; ++q) {
+    dx[q] = xs - (T)(i0 + q) * m.hs;
+    dx2[q] = dx[q] * dx[q];
+    cs[q] = 0;
+    cy[q] = 0;
+  }
+  const T* row = wt + (j0 + m.joff) * m.pw + (i0 + m.ioff);
+#pragma unroll
+  for (int r = 0; r < MW; ++r, row += m.pw) {
+    T w[MW];
+#pragma unroll
+    for (int q = 0; q < MW; ++q) w[q] = row[q];
+    const T dy = ys - (T)(j0 + r) * m.hs;
+    const T dy2 = dy * dy;
+    const T ey = kexp_eval(-dy2);
+    const T lim = k.rc2s - dy2;
+#pragma unroll
+    for (int q = 0; q < MW; ++q) {
+      const T pq = w[q] * ey;
+      const T pm = dx2[q] <= lim ? pq : (T)0;
+      cs[q] += pm;
+      cy[q] += pm * dy;
+    }
+  }
+  T f_[LPP], sx_[LPP], sy_[LPP];
+#pragma unroll
+  for (int j = 0; j < LPP; ++j) {
+    f_[j] = sx_[j] = sy_[j] = 0;
+#pragma unroll
+    for (int q = j; q < MW; q += LPP) {
+      const T ex = kexp_eval(-dx2[q]);
+      const T a = ex * cs[q];
+      f_[j] += a;
+      sx_[j] += a * dx[q];
+      sy_[j] += ex * cy[q];
+    }
+  }
+  f = (f_[0] + f_[1]) + (f_[2] + f_[3]);
+  sx = (sx_[0] + sx_[1]) + (sx_[2] + sx_[3]);
+  sy = (sy_[0] + sy_[1]) + (sy_[2] + sy_[3]);
+}
+
+// Threads of a workgroup: as many waves as the registers of a window allow.
+template <typename T, int MW>
+constexpr int mesh_threads() {
+  return MW == 4 || (sizeof(T) == 4 && MW == 8) ? 1024 : 512;
+}
+// Points of a workgroup: whole waves, over MESH_WGS workgroups at most.
+constexpr int64_t MESH_WGS = 256;
+static inline int64_t mesh_share(int64_t Q) { return ceil_div(ceil_div(Q, MESH_WGS), 64) * 64; }
+
 // Neighbour structure of a call: the binned table (MW = 0) or the dense
 // node weights of the mesh form (MW = window).
 template <typename T>
@@ -481,33 +585,24 @@ __device__ inline void sum_nbr(T xr, T yr, int part, const Nbr<T>& nb, const Eva
   }
 }
 
-template <typename T, bool POSE, int MW>
-__global__ void __launch_bounds__(256) k_eval(const T* __restrict__ pts, int64_t Q, Nbr<T> nb,
-                                              EvalK<T> k0, const double* __restrict__ dpose,
-                                              T* __restrict__ f_out, T* __restrict__ grad_out,
-                                              T* __restrict__ r_out, T* __restrict__ jac_out) {
+// A point's outputs; its LP lanes share the stores.
+template <typename T, bool POSE, int LP>
+__device__ inline void write_point(int64_t i, int part, const EvalK<T>& k, T px, T py, T pz, T zw,
+                                   T f, T sx, T sy, T* __restrict__ f_out,
+                                   T* __restrict__ grad_out, T* __restrict__ r_out,
+                                   T* __restrict__ jac_out) {
   using T2 = typename Vec2<T>::type;
-  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPP;
-  const int part = threadIdx.x % LPP;
-  if (i >= Q) return;  // the lanes of a quad leave together
-  EvalK<T> k = k0;
-  if (POSE) load_pose(k, dpose);
-  T xr, yr, zw, px, py, pz;
-  point_rel<T, POSE>(pts, i, k, xr, yr, zw, px, py, pz);
-  T f, sx, sy;
-  sum_nbr<T, MW>(xr, yr, part, nb, k, f, sx, sy);
   const T fx = sx * k.gscale, fy = sy * k.gscale;
-  // the quad's lanes share the stores
   if (part == 0) f_out[i] = f;
-  if (grad_out && part == 1) {
+  if (grad_out && part == 1 % LP) {
     T2 gv;
     gv.x = fx;
     gv.y = fy;
     reinterpret_cast<T2*>(grad_out)[i] = gv;
   }
   if (POSE) {
-    if (r_out && part == 2) r_out[i] = zw - k.z_off - f;
-    if (jac_out && part == 3) {
+    if (r_out && part == 2 % LP) r_out[i] = zw - k.z_off - f;
+    if (jac_out && part == 3 % LP) {
       // g = (-fx, -fy, 1); q = R^T g; J_rot = p x q
       const T g0 = -fx, g1 = -fy, g2 = (T)1;
       const T q0 = k.R[0] * g0 + k.R[3] * g1 + k.R[6] * g2;
@@ -525,6 +620,47 @@ __global__ void __launch_bounds__(256) k_eval(const T* __restrict__ pts, int64_t
       J[1] = j23;
       J[2] = j45;
     }
+  }
+}
+
+template <typename T, bool POSE, int MW>
+__global__ void __launch_bounds__(256) k_eval(const T* __restrict__ pts, int64_t Q, Nbr<T> nb,
+                                              EvalK<T> k0, const double* __restrict__ dpose,
+                                              T* __restrict__ f_out, T* __restrict__ grad_out,
+                                              T* __restrict__ r_out, T* __restrict__ jac_out) {
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPP;
+  const int part = threadIdx.x % LPP;
+  if (i >= Q) return;  // the lanes of a quad leave together
+  EvalK<T> k = k0;
+  if (POSE) load_pose(k, dpose);
+  T xr, yr, zw, px, py, pz;
+  point_rel<T, POSE>(pts, i, k, xr, yr, zw, px, py, pz);
+  T f, sx, sy;
+  sum_nbr<T, MW>(xr, yr, part, nb, k, f, sx, sy);
+  write_point<T, POSE, LPP>(i, part, k, px, py, pz, zw, f, sx, sy, f_out, grad_out, r_out,
+                            jac_out);
+}
+
+template <typename T, bool POSE, int MW>
+__global__ void __launch_bounds__((mesh_threads<T, MW>())) k_eval_lds(
+    const T* __restrict__ pts, int64_t Q, int64_t share, MeshTab<T> mt, EvalK<T> k0,
+    const double* __restrict__ dpose, T* __restrict__ f_out, T* __restrict__ grad_out,
+    T* __restrict__ r_out, T* __restrict__ jac_out) {
+  extern __shared__ char smem[];
+  T* wt = (T*)smem;
+  const int tid = threadIdx.x;
+  constexpr int NT = mesh_threads<T, MW>();
+  fill_mesh<T>(mt, wt, tid, NT);
+  EvalK<T> k = k0;
+  if (POSE) load_pose(k, dpose);
+  __syncthreads();
+  const int64_t end = min((blockIdx.x + 1) * share, Q);
+  for (int64_t i = blockIdx.x * share + tid; i < end; i += NT) {
+    T xr, yr, zw, px, py, pz;
+    point_rel<T, POSE>(pts, i, k, xr, yr, zw, px, py, pz);
+    T f, sx, sy;
+    sum_lane_mesh<T, MW>(xr, yr, wt, mt.mg, k, f, sx, sy);
+    write_point<T, POSE, 1>(i, 0, k, px, py, pz, zw, f, sx, sy, f_out, grad_out, r_out, jac_out);
   }
 }
 
@@ -558,6 +694,43 @@ __device__ inline void gn_share(int lp, const double (&J)[6], double r, double (
   }
 }
 
+// A point's residual and pose Jacobian row, in FP64.
+template <typename T>
+__device__ inline void gn_row(const EvalK<T>& k, T px, T py, T pz, T zw, T f, T sx, T sy,
+                              double (&J)[6], double& r) {
+  const double fx = (double)sx * (double)k.gscale, fy = (double)sy * (double)k.gscale;
+  r = (double)zw - (double)k.z_off - (double)f;
+  const double g0 = -fx, g1 = -fy, g2 = 1.0;
+  const double q0 = (double)k.R[0] * g0 + (double)k.R[3] * g1 + (double)k.R[6] * g2;
+  const double q1 = (double)k.R[1] * g0 + (double)k.R[4] * g1 + (double)k.R[7] * g2;
+  const double q2 = (double)k.R[2] * g0 + (double)k.R[5] * g1 + (double)k.R[8] * g2;
+  J[0] = (double)py * q2 - (double)pz * q1;
+  J[1] = (double)pz * q0 - (double)px * q2;
+  J[2] = (double)px * q1 - (double)py * q0;
+  J[3] = g0;
+  J[4] = g1;
+  J[5] = g2;
+}
+
+// Term q's sum to its place: J^T J (both triangles), J^T r, r^T r.
+__device__ inline void gn_store(int q, double s, double* __restrict__ JtJ,
+                                double* __restrict__ Jtr, double* __restrict__ rtr) {
+  if (q < 21) {
+    int a = 0, rem = q;
+    while (rem >= 6 - a) {
+      rem -= 6 - a;
+      ++a;
+    }
+    const int b = a + rem;
+    JtJ[a * 6 + b] = s;
+    JtJ[b * 6 + a] = s;
+  } else if (q < 27) {
+    Jtr[q - 21] = s;
+  } else if (rtr) {
+    *rtr = s;
+  }
+}
+
 // Each quad takes points i, i + stride, ... (grid-stride; the launch is a
 // fixed function of Q) and its lanes accumulate their shares of the points'
 // 28 products in FP64 registers (gn_share). The block's sums go through
@@ -579,14 +752,8 @@ __global__ void __launch_bounds__(256) k_eval_gn(const T* __restrict__ pts, int6
     point_rel<T, true>(pts, i, k, xr, yr, zw, px, py, pz);
     T f, sx, sy;
     sum_nbr<T, MW>(xr, yr, lp, nb, k, f, sx, sy);
-    const double fx = (double)sx * (double)k.gscale, fy = (double)sy * (double)k.gscale;
-    const double r = (double)zw - (double)k.z_off - (double)f;
-    const double g0 = -fx, g1 = -fy, g2 = 1.0;
-    const double q0 = (double)k.R[0] * g0 + (double)k.R[3] * g1 + (double)k.R[6] * g2;
-    const double q1 = (double)k.R[1] * g0 + (double)k.R[4] * g1 + (double)k.R[7] * g2;
-    const double q2 = (double)k.R[2] * g0 + (double)k.R[5] * g1 + (double)k.R[8] * g2;
-    const double J[6] = {(double)py * q2 - (double)pz * q1, (double)pz * q0 - (double)px * q2,
-                         (double)px * q1 - (double)py * q0, g0, g1, g2};
+    double J[6], r;
+    gn_row<T>(k, px, py, pz, zw, f, sx, sy, J, r);
     gn_share(lp, J, r, v);
   }
 #pragma unroll
@@ -640,21 +807,69 @@ __global__ void __launch_bounds__(GN_SUM_T) k_eval_gn_sum(const double* __restri
     if (t < o) red[t] += red[t + o];
     __syncthreads();
   }
-  if (t != 0) return;
-  s = red[0];
-  if (q < 21) {
-    int a = 0, rem = q;
-    while (rem >= 6 - a) {
-      rem -= 6 - a;
-      ++a;
+  if (t == 0) gn_store(q, red[0], JtJ, Jtr, rtr);
+}
+
+// Mesh form with the node weights in LDS, one lane per point: the lane adds its
+// point's 28 products itself (the quad's lanes each formed J and took turns
+// with 7). Fixed orders throughout: a lane's points, eight lanes to a run, the
+// runs of a term.
+constexpr int GN_LDS_NT = 512;
+constexpr int64_t GN_LDS_NODES = 20 * 1024;
+template <typename T, int MW>
+__global__ void __launch_bounds__(GN_LDS_NT) k_gn_lds(
+    const T* __restrict__ pts, int64_t Q, int64_t share, MeshTab<T> mt, EvalK<T> k,
+    double* __restrict__ part) {
+  extern __shared__ char smem[];
+  T* wt = (T*)smem;
+  constexpr int NT = GN_LDS_NT, RUNS = NT / 8;
+  const int tid = threadIdx.x;
+  fill_mesh<T>(mt, wt, tid, NT);
+  __syncthreads();
+  double v[GN_TERMS];
+#pragma unroll
+  for (int q = 0; q < GN_TERMS; ++q) v[q] = 0.0;
+  const int64_t end = min((blockIdx.x + 1) * share, Q);
+  for (int64_t i = blockIdx.x * share + tid; i < end; i += NT) {
+    T xr, yr, zw, px, py, pz;
+    point_rel<T, true>(pts, i, k, xr, yr, zw, px, py, pz);
+    T f, sx, sy;
+    sum_lane_mesh<T, MW>(xr, yr, wt, mt.mg, k, f, sx, sy);
+    double J[6], r;
+    gn_row<T>(k, px, py, pz, zw, f, sx, sy, J, r);
+#pragma unroll
+    for (int a = 0, q = 0; a < 6; ++a)
+#pragma unroll
+      for (int b = a; b < 6; ++b, ++q) v[q] += J[a] * J[b];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) v[21 + a] += J[a] * r;
+    v[27] += r * r;
+  }
+  // the LDS serves the reduction from here on: lanes' values, seven terms at
+  // a time, then the runs' sums of all terms
+  double* lv = (double*)smem;                // [thread][7]
+  double* runs = lv + NT * 7;                // [term][run]
+#pragma unroll
+  for (int g = 0; g < GN_TERMS / 7; ++g) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 7; ++q) lv[tid * 7 + q] = v[7 * g + q];
+    __syncthreads();
+    if (tid < 7 * RUNS) {
+      const int tq = tid / RUNS, run = tid % RUNS;
+      double s = 0.0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s += lv[(run * 8 + j) * 7 + tq];
+      runs[(7 * g + tq) * RUNS + run] = s;
     }
-    const int b = a + rem;
-    JtJ[a * 6 + b] = s;
-    JtJ[b * 6 + a] = s;
-  } else if (q < 27) {
-    Jtr[q - 21] = s;
-  } else if (rtr) {
-    *rtr = s;
+  }
+  __syncthreads();
+  if (tid < GN_TERMS * 8) {
+    const int term = tid >> 3;
+    double s = 0.0;
+    for (int j = tid & 7; j < RUNS; j += 8) s += runs[term * RUNS + j];
+    for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 8);
+    if ((tid & 7) == 0) part[term * (int64_t)gridDim.x + blockIdx.x] = s;
   }
 }
 
@@ -1004,6 +1219,50 @@ static void launch_eval(rbf_ctx* ctx, unsigned blocks, int32_t dim, const void* 
                                                           (T*)f, (T*)grad, nullptr, nullptr);
 }
 
+// Whether a call takes the LDS mesh form, and its table. The node array has to
+// fit, and the registers of a window leave a workgroup of 12-node FP64 windows
+// 256 threads only (200,000 points 34.8 us against the quads' 32.2). Whole
+// calls on 100 x 100 centers otherwise, LDS and quads: FP32 1000 points 17.0
+// and 20.2 us, 200,000 17.1 and 19.7, 1,000,000 26 and 42; FP64 16.9 and 19.3,
+// 18.9 and 20.8, 51 and 74.
+template <typename T>
+static bool mesh_lds(const rbf_params* p, const rbf_grid* g, const double* w, bool mesh,
+                     MeshTab<T>* mt) {
+  if (!mesh || g->N <= 0 || (int64_t)table_bytes<T>(g, true) > MESH_LDS_BYTES) return false;
+  if (sizeof(T) == 8 && g->mesh_w > 8) return false;
+  mt->map = g->d_mesh_map;
+  mt->w = w;
+  mt->n = g->mpw * g->mph;
+  mt->mg = mgeom<T>(p, g);
+  return true;
+}
+
+template <typename T, int MW>
+static void launch_eval_lds(rbf_ctx* ctx, int32_t dim, const void* pts, int64_t Q,
+                            const MeshTab<T>& mt, const EvalK<T>& k, const double* dpose, void* f,
+                            void* grad, void* resid, void* jac) {
+  const int64_t share = mesh_share(Q);
+  const unsigned wgs = (unsigned)ceil_div(Q, share);
+  const size_t lds = sizeof(T) * (size_t)mt.n;
+  if (dim == 3)
+    k_eval_lds<T, true, MW><<<wgs, mesh_threads<T, MW>(), lds, ctx->stream>>>(
+        (const T*)pts, Q, share, mt, k, dpose, (T*)f, (T*)grad, (T*)resid, (T*)jac);
+  else
+    k_eval_lds<T, false, MW><<<wgs, mesh_threads<T, MW>(), lds, ctx->stream>>>(
+        (const T*)pts, Q, share, mt, k, nullptr, (T*)f, (T*)grad, nullptr, nullptr);
+}
+
+template <typename T, int MW>
+static void launch_gn_lds(rbf_ctx* ctx, const void* pts, int64_t Q, const MeshTab<T>& mt,
+                          const EvalK<T>& k, double* part) {
+  const int64_t share = mesh_share(Q);
+  constexpr int NT = GN_LDS_NT;
+  const size_t lds = std::max(sizeof(T) * (size_t)mt.n,
+                              sizeof(double) * (NT * 7 + GN_TERMS * (NT / 8)));
+  k_gn_lds<T, MW><<<(unsigned)ceil_div(Q, share), NT, lds, ctx->stream>>>(
+      (const T*)pts, Q, share, mt, k, part);
+}
+
 // Evaluation: the call's table in `tab` (table_bytes<T>(g, mesh) bytes),
 // then one k_eval launch.
 template <typename T>
@@ -1012,9 +1271,24 @@ static rbf_status eval_direct(rbf_ctx* ctx, const rbf_params* p, const rbf_grid*
                               const double* pose, double z_off, void* f, void* grad,
                               void* resid, void* jac, void* tab, bool mesh,
                               const double* dpose = nullptr) {
+  const EvalK<T> k = make_consts<T>(p, g, pose, z_off, mesh);
+  MeshTab<T> mt;
+  if (mesh_lds<T>(p, g, w, mesh, &mt)) {
+    prof_begin(ctx, RBF_PROF_EVAL);
+    switch (g->mesh_w) {
+      case 4: launch_eval_lds<T, 4>(ctx, dim, pts, Q, mt, k, dpose, f, grad, resid, jac); break;
+      case 8: launch_eval_lds<T, 8>(ctx, dim, pts, Q, mt, k, dpose, f, grad, resid, jac); break;
+      default:
+        if constexpr (sizeof(T) == 4)
+          launch_eval_lds<T, 12>(ctx, dim, pts, Q, mt, k, dpose, f, grad, resid, jac);
+        break;
+    }
+    RBF_LAUNCHED(ctx, "k_eval_lds");
+    prof_end(ctx, RBF_PROF_EVAL);
+    return RBF_OK;
+  }
   Nbr<T> nb;
   RBF_TRY(pack_nbr<T>(ctx, p, g, w, tab, mesh, &nb));
-  const EvalK<T> k = make_consts<T>(p, g, pose, z_off, mesh);
   const unsigned blocks = (unsigned)ceil_div(Q * LPP, 256);
   prof_begin(ctx, RBF_PROF_EVAL);
   switch (mesh ? g->mesh_w : 0) {
@@ -1057,9 +1331,31 @@ static rbf_status gn_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g, con
   const bool mesh = g->mesh_w != 0;
   void* tab;
   RBF_TRY(eval_ws<T>(ctx, g, mesh, &tab));
+  const EvalK<T> k = make_consts<T>(p, g, pose, z_off, mesh);
+  MeshTab<T> mt;
+  // A Gauss-Newton workgroup has 512 threads: not for more nodes than these
+  // fill quickly (36,481 nodes, FP32, 200,000 points 23.2 us against the quads'
+  // 21.7), for the registers of 12-node windows (24.7 against 22.5), or for an
+  // FP64 workgroup's second pass over its lanes (200,000 points 23.3 against
+  // 21.0). Else, LDS and quads: FP32 1000 points 19.5 and 20.9, 200,000 18.1
+  // and 21.3, 1,000,000 33 and 39; FP64 100,000 points 18.8 and 21.2.
+  if (g->mesh_w <= 8 && (int64_t)g->mpw * g->mph <= GN_LDS_NODES &&
+      (sizeof(T) == 4 || Q <= MESH_WGS * GN_LDS_NT) && mesh_lds<T>(p, g, w, mesh, &mt)) {
+    rbf_status st;
+    double* part = (double*)ws_get(ctx, WS_TMP3, sizeof(double) * GN_TERMS * MESH_WGS, &st);
+    if (!part) return st;
+    switch (g->mesh_w) {
+      case 4: launch_gn_lds<T, 4>(ctx, pts, Q, mt, k, part); break;
+      default: launch_gn_lds<T, 8>(ctx, pts, Q, mt, k, part); break;
+    }
+    RBF_LAUNCHED(ctx, "k_gn_lds");
+    k_eval_gn_sum<<<GN_TERMS, GN_SUM_T, 0, ctx->stream>>>(
+        part, ceil_div(Q, mesh_share(Q)), JtJ, Jtr, rtr);
+    RBF_LAUNCHED(ctx, "k_eval_gn_sum");
+    return RBF_OK;
+  }
   Nbr<T> nb;
   RBF_TRY(pack_nbr<T>(ctx, p, g, w, tab, mesh, &nb));
-  const EvalK<T> k = make_consts<T>(p, g, pose, z_off, mesh);
   int64_t blocks = ceil_div(Q * LPP, 256);
   if (blocks > GN_MAX_BLOCKS) blocks = GN_MAX_BLOCKS;
   rbf_status st;

@@ -1,0 +1,70 @@
+"""Mesh form with the node weights in LDS, on both sides of its rules (node
+arrays that fit, points of a Gauss-Newton call) and for every window width,
+against the quad form: the same centers and one more far away, whose node array
+fits no LDS.
+
+Evaluation: both forms take every sum in the same order, so the outputs are
+equal bit for bit. Gauss-Newton: the per-point terms are equal and their FP64
+sums differ by at most 2 Q eps times the sums of their absolute values, at
+most sqrt(A_aa A_bb) for term (a, b) of the Gram matrix A of (J, r)."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import dev, host
+from paper_2509_26222_amd import api, synth
+
+pytestmark = pytest.mark.gpu
+EPS = np.finfo(np.float64).eps
+
+
+# node arrays (with the margins of the window's width): 116 x 116 nodes;
+# FP32 up to 38,912 nodes, FP64 up to 19,456
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("res,nx,ny,Q", [
+    (0.5, 100, 100, 1), (0.5, 100, 100, 64), (0.5, 100, 100, 16_385),
+    (0.5, 100, 100, 131_072), (0.5, 100, 100, 131_073), (0.5, 30, 30, 300_001),
+    (1.0, 40, 33, 40_000), (0.3, 60, 41, 40_000), (0.5, 1, 1, 20_000),
+    (0.5, 240, 136, 20_000), (0.5, 240, 137, 20_000),   # 256 x 152 = 38,912, 256 x 153
+    (0.5, 240, 60, 20_000), (0.5, 240, 61, 20_000)])    # 256 x 76 = 19,456, 256 x 77
+def test_lds_equals_quads(ctx, dtype, res, nx, ny, Q):
+    p = api.Params()
+    rng = np.random.default_rng(Q + nx)
+    c = synth.grid_centers(rng, nx, ny, res, jitter=0.0)
+    keep = rng.random(c.shape[0]) < 0.9
+    keep[[0, -1]] = True
+    c = np.ascontiguousarray(c[keep])
+    grid = ctx.grid(p, dev(c)).set_mesh_roi((0.0, 0.0), res)
+    far = ctx.grid(p, dev(np.concatenate([c, [[399.5 * res, 299.5 * res]]])))
+    far.set_mesh_roi((0.0, 0.0), res)
+    w = dev(rng.normal(size=c.shape[0]))
+    wf = torch.cat([w, torch.ones_like(w[:1])])
+    R, t = synth.rot_zyx(0.4, 0.05, -0.02), np.array([0.3, -0.2, 0.6])
+    world = np.concatenate([rng.uniform(-2.0, [nx * res + 2.0, ny * res + 2.0], size=(Q, 2)),
+                            rng.normal(size=(Q, 1))], 1)
+    world[7:9, :2] = c[0]                      # on a node
+    xyz = (world - t) @ R
+    if Q > 64:
+        xyz[20:25, 0] = [np.nan, np.inf, -np.inf, 1e30, -1e9]
+    body = dev(xyz).to(dtype)
+    flat = dev(world[:, :2]).to(dtype).contiguous()
+    print(f"window of {res}: {nx} x {ny} nodes, {Q} points", flush=True)
+    for pts, pose in ((body, (R, t)), (flat, None)):
+        got = ctx.eval(p, grid, w, pts, pose=pose, z_off=0.1 if pose else 0.0)
+        ref = ctx.eval(p, far, wf, pts, pose=pose, z_off=0.1 if pose else 0.0)
+        for key, v in got.items():
+            if v is None:
+                continue
+            r = ref[key]
+            assert torch.equal(v.view(torch.int32 if dtype == torch.float32 else torch.int64),
+                               r.view(torch.int32 if dtype == torch.float32 else torch.int64))
+    body[20:25] = body[10:15]
+    A, b, rr = ctx.eval_gn(p, grid, w, body, (R, t), 0.1)
+    A0, b0, rr0 = (host(q) for q in ctx.eval_gn(p, far, wf, body, (R, t), 0.1))
+    lim = 2 * Q * EPS
+    d = np.sqrt(np.diag(A0))
+    assert np.all(np.abs(host(A) - A0) <= lim * np.outer(d, d) + 1e-300)
+    assert np.all(np.abs(host(b) - b0) <= lim * d * np.sqrt(rr0) + 1e-300)
+    assert abs(host(rr) - rr0) <= lim * rr0
+    again = ctx.eval_gn(p, grid, w, body, (R, t), 0.1)
+    assert all(torch.equal(x, y) for x, y in zip((A, b, rr), again))
