@@ -82,6 +82,11 @@ struct EGeom {
 };
 constexpr float EVAL_PAD = 1.0f / 64.0f;
 
+// Fused multiply-adds written out where several kernels have to round alike
+// (left to the compiler, the choice of the product to fuse varies).
+__device__ inline double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ inline float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
 __device__ inline double kexp_eval(double a) { return exp(a); }
 __device__ inline float kexp_eval(float a) { return __builtin_amdgcn_exp2f(a); }
 
@@ -223,15 +228,23 @@ __device__ inline void quad_runs(float u, float v, int part, const EGeom& g,
 // clamp; it is masked out by its index).
 template <typename T>
 struct TabReader {
+  static constexpr bool AHEAD = false;
+  using Slot = typename Vec4<T>::type;
   __amdgpu_buffer_rsrc_t r;
   __device__ TabReader(const typename Vec4<T>::type* tab, int64_t n) {
     r = __builtin_amdgcn_make_buffer_rsrc((void*)tab, (short)0,
                                           (int)(n * (int64_t)sizeof(typename Vec4<T>::type)),
                                           0x00020000);
   }
-  // (x', y', w) of entry a, and its original index if IDX
+  // (x', y', w) of entry a + u, and its original index if IDX
   template <bool IDX>
-  __device__ typename Vec4<T>::type load(int a, int off) const;
+  __device__ Slot load(int a, int off) const;
+  template <bool IDX>
+  __device__ Slot fetch(int a, int u) const {
+    return load<IDX>(a, u * (int)sizeof(Slot));
+  }
+  __device__ void complete(Slot&) const {}
+  __device__ Slot value(const Slot& s) const { return s; }
 };
 // (One 16-byte load; the compiler narrows it to the components used.)
 template <>
@@ -260,6 +273,50 @@ __device__ inline double4 TabReader<double>::load(int a, int off) const {
   return c;
 }
 
+// The same entries formed from the grid's arrays and the weights as they are
+// read: no packing launch, one more load behind the index. The operations are
+// those of k_pack_centers.
+template <typename T>
+struct RawReader {
+  static constexpr bool AHEAD = true;
+  using Out = typename Vec4<T>::type;
+  struct Slot {
+    double2 xy;
+    int32_t i;
+    double w;
+  };
+  __amdgpu_buffer_rsrc_t rc, ri, rw;
+  double x0, y0, ks;
+  __device__ RawReader(const double* ecxy, const int32_t* eidx, const double* w, int64_t n,
+                       double x0_, double y0_, double ks_)
+      : x0(x0_), y0(y0_), ks(ks_) {
+    rc = __builtin_amdgcn_make_buffer_rsrc((void*)ecxy, (short)0, (int)(n * 16), 0x00020000);
+    ri = __builtin_amdgcn_make_buffer_rsrc((void*)eidx, (short)0, (int)(n * 4), 0x00020000);
+    rw = __builtin_amdgcn_make_buffer_rsrc((void*)w, (short)0, (int)(n * 8), 0x00020000);
+  }
+  template <bool IDX>
+  __device__ Slot fetch(int a, int u) const {
+    Slot s;
+    s.xy = __builtin_bit_cast(double2,
+                              __builtin_amdgcn_raw_buffer_load_b128(rc, a * 16 + u * 16, 0, 0));
+    s.i = (int)__builtin_amdgcn_raw_buffer_load_b32(ri, a * 4 + u * 4, 0, 0);
+    s.w = 0.0;
+    return s;
+  }
+  __device__ void complete(Slot& s) const {
+    s.w = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rw, s.i * 8, 0, 0));
+  }
+  __device__ Out value(const Slot& s) const {
+#pragma clang fp contract(off)
+    Out c;
+    c.x = (T)((s.xy.x - x0) * ks);
+    c.y = (T)((s.xy.y - y0) * ks);
+    c.z = (T)s.w;
+    c.w = idx_bits(s.i, T(0));
+    return c;
+  }
+};
+
 // Candidates per lane and step: the table loads of EU candidates (4 apart,
 // the quad covering 4 EU consecutive entries) are issued together; a slot
 // past the run is masked out.
@@ -269,28 +326,51 @@ constexpr int eval_unroll() { return 2; }
 // This lane's share of the point's candidates: in every run, the entries
 // s0 + part, s0 + part + 4, ...; op(c, dx', dy', e) with e = phi, or 0
 // outside the support (and for masked slots). c.w holds the original index
-// only if IDX.
-template <typename T, bool IDX, typename Op>
-__device__ inline void for_candidates(T xs, T ys, const TabReader<T>& tab,
+// only if IDX. Tab::AHEAD: the first step of a run is loaded while the run
+// before it is summed (a load past a run's end is not used), so that a point's
+// eight runs do not wait for memory one after the other; with enough
+// wavefronts to hide the waits the registers it takes cost more.
+template <typename T, bool IDX, typename Tab, typename Op>
+__device__ inline void for_candidates(T xs, T ys, const Tab& tab,
                                       const int (&s0)[EVAL_MAX_ROWS],
                                       const int (&s1)[EVAL_MAX_ROWS], int part, T rc2s,
                                       Op op) {
   constexpr int EU = eval_unroll<T>();
-  constexpr int STEP = (int)sizeof(typename Vec4<T>::type) * LPP;  // bytes between a lane's slots
+  typename Tab::Slot next[EU];
+  if constexpr (Tab::AHEAD) {
+#pragma unroll
+    for (int u = 0; u < EU; ++u) next[u] = tab.template fetch<IDX>(s0[0] + part, u * LPP);
+  }
 #pragma unroll
   for (int k = 0; k < EVAL_MAX_ROWS; ++k) {
     const int e = s1[k];
-    for (int a = s0[k] + part; a < e; a += EU * LPP) {
-      typename Vec4<T>::type c[EU];
-#pragma unroll
-      for (int u = 0; u < EU; ++u) c[u] = tab.template load<IDX>(a, u * STEP);
+    typename Tab::Slot s[EU];
+    if constexpr (Tab::AHEAD) {
 #pragma unroll
       for (int u = 0; u < EU; ++u) {
-        const T dx = xs - c[u].x, dy = ys - c[u].y;
-        const T d2 = dx * dx + dy * dy;
+        s[u] = next[u];
+        tab.complete(s[u]);
+      }
+      if (k + 1 < EVAL_MAX_ROWS)
+#pragma unroll
+        for (int u = 0; u < EU; ++u) next[u] = tab.template fetch<IDX>(s0[k + 1] + part, u * LPP);
+    }
+    for (int a = s0[k] + part; a < e; a += EU * LPP) {
+      if (!Tab::AHEAD || a != s0[k] + part) {
+#pragma unroll
+        for (int u = 0; u < EU; ++u) {
+          s[u] = tab.template fetch<IDX>(a, u * LPP);
+          tab.complete(s[u]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < EU; ++u) {
+        const typename Vec4<T>::type c = tab.value(s[u]);
+        const T dx = xs - c.x, dy = ys - c.y;
+        const T d2 = fma_t(dx, dx, dy * dy);
         const T e0 = kexp_eval(-d2);
         const T ph = ((u == 0 || a + u * LPP < e) && d2 <= rc2s) ? e0 : (T)0;
-        op(c[u], dx, dy, ph);
+        op(c, dx, dy, ph);
       }
     }
   }
@@ -332,8 +412,8 @@ __device__ inline void load_pose(EvalK<T>& k, const double* __restrict__ dpose) 
 
 // f, sum w phi dx', sum w phi dy' at a point (coordinates relative to the
 // grid origin), summed over the quad: every lane of the quad gets them.
-template <typename T>
-__device__ inline void sum_point(T xr, T yr, int part, const TabReader<T>& tab,
+template <typename T, typename Tab>
+__device__ inline void sum_point(T xr, T yr, int part, const Tab& tab,
                                  const int32_t* __restrict__ estart, const EGeom& g,
                                  const EvalK<T>& k, T& f, T& sx, T& sy) {
   int s0[EVAL_MAX_ROWS], s1[EVAL_MAX_ROWS];
@@ -342,9 +422,9 @@ __device__ inline void sum_point(T xr, T yr, int part, const TabReader<T>& tab,
   for_candidates<T, false>(xr * k.ks, yr * k.ks, tab, s0, s1, part, k.rc2s,
                     [&](const typename Vec4<T>::type& c, T dx, T dy, T e) {
                       const T we = c.z * e;
-                      f_ += we;
-                      sx_ += we * dx;
-                      sy_ += we * dy;
+                      f_ = fma_t(c.z, e, f_);
+                      sx_ = fma_t(we, dx, sx_);
+                      sy_ = fma_t(we, dy, sy_);
                     });
   f = quad_sum(f_);
   sx = quad_sum(sx_);
@@ -562,8 +642,8 @@ constexpr int mesh_threads() {
 constexpr int64_t MESH_WGS = 256;
 static inline int64_t mesh_share(int64_t Q) { return ceil_div(ceil_div(Q, MESH_WGS), 64) * 64; }
 
-// Neighbour structure of a call: the binned table (MW = 0) or the dense
-// node weights of the mesh form (MW = window).
+// Neighbour structure of a call: the binned table (MW = 0), the grid's arrays
+// (MW = -1) or the dense node weights of the mesh form (MW = window).
 template <typename T>
 struct Nbr {
   const void* tab;        // packed table (n entries) or node weights (n nodes)
@@ -571,6 +651,10 @@ struct Nbr {
   const int32_t* estart;  // binned form
   EGeom eg;               // binned form
   MGeom<T> mg;            // mesh form
+  const double* ecxy;     // binned form read as it is (MW = -1)
+  const int32_t* eidx;
+  const double* w;
+  double x0, y0, ks;
 };
 
 template <typename T, int MW>
@@ -578,6 +662,9 @@ __device__ inline void sum_nbr(T xr, T yr, int part, const Nbr<T>& nb, const Eva
                                T& sx, T& sy) {
   if constexpr (MW == 0) {
     const TabReader<T> tab((const typename Vec4<T>::type*)nb.tab, nb.n);
+    sum_point<T>(xr, yr, part, tab, nb.estart, nb.eg, k, f, sx, sy);
+  } else if constexpr (MW < 0) {
+    const RawReader<T> tab(nb.ecxy, nb.eidx, nb.w, nb.n, nb.x0, nb.y0, nb.ks);
     sum_point<T>(xr, yr, part, tab, nb.estart, nb.eg, k, f, sx, sy);
   } else {
     const MeshReader<T> wt((const T*)nb.tab, nb.n);
@@ -925,8 +1012,8 @@ __global__ void __launch_bounds__(PLANES ? ADJ_NT : 256) k_eval_adjoint(
     for_candidates<T, true>(xr * k.ks, yr * k.ks, tab, s0, s1, part, k.rc2s,
                             [&](const typename Vec4<T>::type& c, T dx, T dy, T e) {
                         const T we = c.z * e;
-                        sx += we * dx;
-                        sy += we * dy;
+                        sx = fma_t(we, dx, sx);
+                        sy = fma_t(we, dy, sy);
                         if (scatter && e != (T)0) {
                           if (PLANES)
                             atomicAdd(&hw[bits_idx(c.w)], (double)(a * e));
@@ -1186,13 +1273,31 @@ rbf_status eval_workspace(rbf_ctx* ctx, const rbf_grid* g) {
   return RBF_OK;
 }
 
+// Binned calls of at most this many points read the grid's arrays as they are.
+// Whole calls on 10,000 centers, so and packed: FP64 1000 points 13 and 17 us,
+// 64,000 15 and 17, 100,000 23 and 21; FP32 64,000 14 and 16, 100,000 21 and 18
+// (with a launch saved the smaller ones are bound by the host). Alone, 1000
+// FP64 points on 400 centers: 13.4 -> 9.3 us.
+constexpr int64_t EVAL_RAW_Q = 65536;
+
 // The table of one call in `tab`: the mesh form's node weights if mesh,
 // else the packed (x', y', w, index) of the eval-sorted centers.
 template <typename T>
 static rbf_status pack_nbr(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g,
-                           const double* w, void* tab, bool mesh, Nbr<T>* nb) {
+                           const double* w, void* tab, bool mesh, bool raw, Nbr<T>* nb) {
   nb->tab = tab;
   nb->estart = g->d_estart;
+  if (raw) {
+    nb->n = g->N;
+    nb->eg = egeom(p, g);
+    nb->ecxy = g->d_ecxy;
+    nb->eidx = g->d_eidx;
+    nb->w = w;
+    nb->x0 = g->x0;
+    nb->y0 = g->y0;
+    nb->ks = coord_scale(p, sizeof(T) == 4);
+    return RBF_OK;
+  }
   if (mesh) {
     nb->n = (int64_t)g->mpw * g->mph;
     nb->mg = mgeom<T>(p, g);
@@ -1287,11 +1392,13 @@ static rbf_status eval_direct(rbf_ctx* ctx, const rbf_params* p, const rbf_grid*
     prof_end(ctx, RBF_PROF_EVAL);
     return RBF_OK;
   }
+  const bool raw = !mesh && Q <= EVAL_RAW_Q;
   Nbr<T> nb;
-  RBF_TRY(pack_nbr<T>(ctx, p, g, w, tab, mesh, &nb));
+  RBF_TRY(pack_nbr<T>(ctx, p, g, w, tab, mesh, raw, &nb));
   const unsigned blocks = (unsigned)ceil_div(Q * LPP, 256);
   prof_begin(ctx, RBF_PROF_EVAL);
-  switch (mesh ? g->mesh_w : 0) {
+  switch (mesh ? g->mesh_w : raw ? -1 : 0) {
+    case -1: launch_eval<T, -1>(ctx, blocks, dim, pts, Q, nb, k, dpose, f, grad, resid, jac); break;
     case 0: launch_eval<T, 0>(ctx, blocks, dim, pts, Q, nb, k, dpose, f, grad, resid, jac); break;
     case 4: launch_eval<T, 4>(ctx, blocks, dim, pts, Q, nb, k, dpose, f, grad, resid, jac); break;
     case 8: launch_eval<T, 8>(ctx, blocks, dim, pts, Q, nb, k, dpose, f, grad, resid, jac); break;
@@ -1354,15 +1461,17 @@ static rbf_status gn_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g, con
     RBF_LAUNCHED(ctx, "k_eval_gn_sum");
     return RBF_OK;
   }
+  const bool raw = !mesh && Q <= EVAL_RAW_Q;
   Nbr<T> nb;
-  RBF_TRY(pack_nbr<T>(ctx, p, g, w, tab, mesh, &nb));
+  RBF_TRY(pack_nbr<T>(ctx, p, g, w, tab, mesh, raw, &nb));
   int64_t blocks = ceil_div(Q * LPP, 256);
   if (blocks > GN_MAX_BLOCKS) blocks = GN_MAX_BLOCKS;
   rbf_status st;
   double* part = (double*)ws_get(ctx, WS_TMP3, sizeof(double) * GN_TERMS * (size_t)blocks, &st);
   if (!part) return st;
   const dim3 gr((unsigned)blocks);
-  switch (mesh ? g->mesh_w : 0) {
+  switch (mesh ? g->mesh_w : raw ? -1 : 0) {
+    case -1: k_eval_gn<T, -1><<<gr, 256, 0, ctx->stream>>>((const T*)pts, Q, nb, k, part); break;
     case 0: k_eval_gn<T, 0><<<gr, 256, 0, ctx->stream>>>((const T*)pts, Q, nb, k, part); break;
     case 4: k_eval_gn<T, 4><<<gr, 256, 0, ctx->stream>>>((const T*)pts, Q, nb, k, part); break;
     case 8: k_eval_gn<T, 8><<<gr, 256, 0, ctx->stream>>>((const T*)pts, Q, nb, k, part); break;

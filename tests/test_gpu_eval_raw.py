@@ -1,0 +1,39 @@
+"""Binned evaluation of few points, read from the grid's arrays without the
+packed table, against the packed form, which a call of more points takes: the
+same operations on the same values in the same order, so the outputs are equal
+bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import dev
+from paper_2509_26222_amd import api, synth
+
+pytestmark = pytest.mark.gpu
+LIMIT = 65536  # largest call that reads the arrays as they are
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("nx,ny,res,Q", [(1, 1, 0.5, 1), (20, 20, 0.5, 1000), (60, 50, 0.2, 3001),
+                                         (99, 101, 0.5, LIMIT)])
+def test_raw_equals_packed(ctx, dtype, nx, ny, res, Q):
+    p = api.Params()
+    rng = np.random.default_rng(nx + Q)
+    c = synth.grid_centers(rng, nx, ny, res, jitter=0.2 * res)
+    grid = ctx.grid(p, dev(c))
+    w = dev(rng.normal(size=c.shape[0]))
+    R, t = synth.rot_zyx(0.4, 0.05, -0.02), np.array([0.3, -0.2, 0.6])
+    n = LIMIT + 1
+    world = np.concatenate([rng.uniform(-2.0, [nx * res + 2.0, ny * res + 2.0], size=(n, 2)),
+                            rng.normal(size=(n, 1))], 1)
+    xyz = (world - t) @ R
+    if Q > 64:
+        xyz[20:25, 0] = [np.nan, np.inf, -np.inf, 1e30, -1e9]
+    bits = torch.int32 if dtype == torch.float32 else torch.int64
+    for pts, pose in ((dev(xyz).to(dtype), (R, t)),
+                      (dev(world[:, :2]).to(dtype).contiguous(), None)):
+        full = ctx.eval(p, grid, w, pts, pose=pose)
+        part = ctx.eval(p, grid, w, pts[:Q], pose=pose)
+        for key, v in part.items():
+            if v is not None:
+                assert torch.equal(v.view(bits), full[key][:Q].view(bits)), key
