@@ -205,7 +205,9 @@ rbf_status rbf_bin_centers(rbf_ctx* ctx, const double* centers, int64_t N,
  * a dense node array, with one exponential per window row and column
  * instead of one per candidate. Results equal the binned form up to
  * rounding (the support test is taken on the same scaled squared
- * distance). rbf_eval_adjoint and the assembly keep the binned form.
+ * distance). So does rbf_eval_adjoint in FP64 where a call has enough points
+ * to sum the weights' gradient on chip; else it and the assembly keep the
+ * binned form.
  * res = 0 returns the grid to the binned form. The dense node array covers
  * the centers' node range plus a margin of the window width: at most
  * 16384 nodes per axis and 2^26 in all; the support may span at most 12

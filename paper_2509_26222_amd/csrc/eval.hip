@@ -970,25 +970,80 @@ __global__ void __launch_bounds__(GN_LDS_NT) k_gn_lds(
 // in a plane of its own, which k_adjoint_sum adds up. Else every addition is a
 // device atomic, and these bound the kernel (5.6 million of them at 200,000
 // points). 200,000 FP64 points, 10,000 centers: 192 us with device atomics,
-// 40 + 7 us with planes, bound by the FP64 exponentials of the candidates.
+// 40 + 7 us with planes (31 + 7 by the mesh form), bound by the FP64
+// exponentials of the candidates and the LDS additions.
 constexpr int64_t ADJ_PLANES = 256;            // one workgroup per CU
 constexpr int ADJ_NT = 1024;                   // its threads (four waves per SIMD)
 constexpr int64_t ADJ_LDS_N = 18 * 1024;       // 144 KB of sums
 constexpr int64_t ADJ_MIN_PLANES = 16;         // 256 points each
 
-template <typename T, bool POSE, bool PLANES>
+// Mesh form of a point's share in the planes form: sum w phi dx', sum w phi dy'
+// and a phi added to the nodes of hw (a node without a center collects what
+// k_adjoint_sum leaves out). Laid out as sum_point_mesh; one exponential per
+// window row and column instead of one per candidate.
+template <typename T, int MW>
+__device__ inline void adjoint_point_mesh(T xr, T yr, int part, const MeshReader<T>& wt,
+                                          const MGeom<T>& m, const EvalK<T>& k, T a, bool scatter,
+                                          double* hw, T& sx, T& sy) {
+  constexpr int CPL = MW / LPP;
+  const float u = (float)(xr * m.inv_res), v = (float)(yr * m.inv_res);
+  const bool ok = fabsf(u) < 16777216.f && fabsf(v) < 16777216.f;  // also NaN
+  const int i0 = ok ? min(max((int)ceilf(u - m.rp), m.ilo), m.ihi) : m.ilo;
+  const int j0 = ok ? min(max((int)ceilf(v - m.rp), m.jlo), m.jhi) : m.jlo;
+  const T xs = ok ? xr * k.ks : (T)1e18, ys = ok ? yr * k.ks : (T)1e18;
+  T dx[CPL], dx2[CPL], ex[CPL], cs[CPL], cy[CPL], eown[CPL];
+#pragma unroll
+  for (int q = 0; q < CPL; ++q) {
+    dx[q] = xs - (T)(i0 + part + LPP * q) * m.hs;
+    dx2[q] = dx[q] * dx[q];
+    ex[q] = kexp_eval(-dx2[q]);
+    cs[q] = 0;
+    cy[q] = 0;
+    const T dyq = ys - (T)(j0 + part + LPP * q) * m.hs;
+    eown[q] = kexp_eval(-(dyq * dyq));
+  }
+  constexpr int SZ = (int)sizeof(T);
+  const int node = (j0 + m.joff) * m.pw + (i0 + m.ioff + part);
+#pragma unroll
+  for (int r = 0; r < MW; ++r) {
+    const T dy = ys - (T)(j0 + r) * m.hs;
+    const T ey = quad_bcast_any(eown[r / LPP], r % LPP);
+    const T lim = k.rc2s - dy * dy;  // node in the support iff dx'^2 <= lim
+    T w[CPL];
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) w[q] = wt.load(node * SZ + q * LPP * SZ, r * m.pw * SZ);
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+      const bool in = dx2[q] <= lim;
+      const T pm = in ? w[q] * ey : (T)0;
+      cs[q] += pm;
+      cy[q] += pm * dy;
+      if (scatter && in) atomicAdd(&hw[node + q * LPP + r * m.pw], (double)(a * (ex[q] * ey)));
+    }
+  }
+  T sx_ = 0, sy_ = 0;
+#pragma unroll
+  for (int q = 0; q < CPL; ++q) {
+    sx_ += ex[q] * cs[q] * dx[q];
+    sy_ += ex[q] * cy[q];
+  }
+  sx = quad_sum(sx_);
+  sy = quad_sum(sy_);
+}
+
+// MW: 0, the binned form, or (PLANES) the mesh form's window.
+template <typename T, bool POSE, bool PLANES, int MW>
 __global__ void __launch_bounds__(PLANES ? ADJ_NT : 256) k_eval_adjoint(
-    const T* __restrict__ pts, int64_t Q, const typename Vec4<T>::type* __restrict__ tab0,
-    int64_t N, const int32_t* __restrict__ estart, EGeom g, EvalK<T> k0,
+    const T* __restrict__ pts, int64_t Q, Nbr<T> nb, EvalK<T> k0,
     const double* __restrict__ dpose,
     const T* __restrict__ gbar_f, const T* __restrict__ gbar_r, T* __restrict__ d_pts,
     double* __restrict__ d_w, double* __restrict__ d_pose) {
   constexpr int NT = PLANES ? ADJ_NT : 256, PPB = NT / LPP;
   extern __shared__ double hw[];  // PLANES: this workgroup's dL/dw
+  const int64_t N = nb.n;
   const int part = threadIdx.x % LPP;
   EvalK<T> k = k0;
   if (POSE) load_pose(k, dpose);
-  const TabReader<T> tab(tab0, N);
   double acc[6] = {0, 0, 0, 0, 0, 0};
   int64_t i = (int64_t)blockIdx.x * PPB + threadIdx.x / LPP, end = i + 1;
   if (PLANES) {
@@ -1005,24 +1060,30 @@ __global__ void __launch_bounds__(PLANES ? ADJ_NT : 256) k_eval_adjoint(
     const T gf = gbar_f ? gbar_f[i] : (T)0;
     const T gr = (POSE && gbar_r) ? gbar_r[i] : (T)0;
     const T a = gf - gr;
-    int s0[EVAL_MAX_ROWS], s1[EVAL_MAX_ROWS];
-    quad_runs((float)(xr * k.inv_eh), (float)(yr * k.inv_eh), part, g, estart, s0, s1);
     T sx = 0, sy = 0;
     const bool scatter = d_w && a != (T)0;
-    for_candidates<T, true>(xr * k.ks, yr * k.ks, tab, s0, s1, part, k.rc2s,
-                            [&](const typename Vec4<T>::type& c, T dx, T dy, T e) {
-                        const T we = c.z * e;
-                        sx = fma_t(we, dx, sx);
-                        sy = fma_t(we, dy, sy);
-                        if (scatter && e != (T)0) {
-                          if (PLANES)
-                            atomicAdd(&hw[bits_idx(c.w)], (double)(a * e));
-                          else
-                            atomicAdd(&d_w[bits_idx(c.w)], (double)(a * e));
-                        }
-                      });
-    sx = quad_sum(sx);
-    sy = quad_sum(sy);
+    if constexpr (MW == 0) {
+      const TabReader<T> tab((const typename Vec4<T>::type*)nb.tab, N);
+      int s0[EVAL_MAX_ROWS], s1[EVAL_MAX_ROWS];
+      quad_runs((float)(xr * k.inv_eh), (float)(yr * k.inv_eh), part, nb.eg, nb.estart, s0, s1);
+      for_candidates<T, true>(xr * k.ks, yr * k.ks, tab, s0, s1, part, k.rc2s,
+                              [&](const typename Vec4<T>::type& c, T dx, T dy, T e) {
+                          const T we = c.z * e;
+                          sx = fma_t(we, dx, sx);
+                          sy = fma_t(we, dy, sy);
+                          if (scatter && e != (T)0) {
+                            if (PLANES)
+                              atomicAdd(&hw[bits_idx(c.w)], (double)(a * e));
+                            else
+                              atomicAdd(&d_w[bits_idx(c.w)], (double)(a * e));
+                          }
+                        });
+      sx = quad_sum(sx);
+      sy = quad_sum(sy);
+    } else {
+      const MeshReader<T> wt((const T*)nb.tab, N);
+      adjoint_point_mesh<T, MW>(xr, yr, part, wt, nb.mg, k, a, scatter, hw, sx, sy);
+    }
     const T fx = sx * k.gscale, fy = sy * k.gscale;
     const T dx0 = a * fx, dx1 = a * fy, dx2 = gr;
     if (POSE) {
@@ -1069,9 +1130,11 @@ __global__ void __launch_bounds__(PLANES ? ADJ_NT : 256) k_eval_adjoint(
   }
 }
 
-// d_w += the planes: 64 centers per workgroup, 16 waves over the planes.
+// d_w += the planes: 64 centers per workgroup, 16 waves over the planes. map:
+// the center of each of the N nodes (mesh form), or null.
 __global__ void __launch_bounds__(1024) k_adjoint_sum(const double* __restrict__ plane,
                                                       int planes, int64_t N,
+                                                      const int32_t* __restrict__ map,
                                                       double* __restrict__ d_w) {
   __shared__ double s[16][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -1083,7 +1146,8 @@ __global__ void __launch_bounds__(1024) k_adjoint_sum(const double* __restrict__
   __syncthreads();
   if (w != 0 || e >= N) return;
   for (int q = 1; q < 16; ++q) v += s[q][lane];
-  if (v != 0.0) atomicAdd(&d_w[e], v);  // other calls may add to d_w at the same time
+  const int64_t c = map ? map[e] : e;
+  if (c >= 0 && v != 0.0) atomicAdd(&d_w[c], v);  // other calls may add to d_w at the same time
 }
 
 // ---- pose increments on SO(3) x R^3 (differentiation form)
@@ -1249,19 +1313,6 @@ static rbf_status pack_into(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g
   k_pack_centers<T><<<ceil_div(g->N, 256), 256, 0, ctx->stream>>>(
       g->d_ecxy, g->d_eidx, w, g->N, g->x0, g->y0, coord_scale(p, sizeof(T) == 4), tab);
   RBF_LAUNCHED(ctx, "k_pack_centers");
-  return RBF_OK;
-}
-
-// The same in the context's workspace.
-template <typename T>
-static rbf_status pack(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g, const double* w,
-                       typename Vec4<T>::type** tab_out) {
-  rbf_status st;
-  auto* tab = (typename Vec4<T>::type*)ws_get(ctx, WS_TMP2,
-                                               sizeof(typename Vec4<T>::type) * g->N, &st);
-  if (!tab) return st;
-  RBF_TRY(pack_into<T>(ctx, p, g, w, tab));
-  *tab_out = tab;
   return RBF_OK;
 }
 
@@ -1488,45 +1539,58 @@ static rbf_status adjoint_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g
                             const double* w, const void* pts, int64_t Q, int32_t dim,
                             const double* pose, const void* gf, const void* gr, void* d_pts,
                             double* d_w, double* d_pose, const double* dpose = nullptr) {
-  typename Vec4<T>::type* tab;
-  RBF_TRY(pack<T>(ctx, p, g, w, &tab));
-  const EvalK<T> k = make_consts<T>(p, g, pose, 0.0);
-  const EGeom eg = egeom(p, g);
   // Planes when the sums fit the LDS and the points outweigh clearing, writing
   // and adding up N sums per plane. Whole calls by planes and by atomics:
   // N = 400, 2048 points 24 and 24 us, 8192 21 and 66; N = 10,000, 8192
   // points 20 and 18, 20,000 22 and 27, 200,000 43 and 184; N = 17,956,
   // 20,000 points 27 and 26, 50,000 34 and 51 (FP32).
-  // The buffer's size depends on N alone, so that it grows with the grid's
-  // size only, as the table's; not taken if it would grow during a capture.
+  // The buffer's size depends on the grid alone, so that it grows with the
+  // grid's size only, as the table's; not taken if it would grow during a
+  // capture.
   const int64_t planes = std::min<int64_t>(ADJ_PLANES, Q / 256);
+  const int64_t nodes = (int64_t)g->mpw * g->mph;
+  // In FP64 on a mesh with windows of up to 8 nodes (the registers of a 12-node
+  // window do not fit 1024 threads) also by the mesh form: 200,000 points on
+  // 10,000 centers 40 -> 31 us. FP32 keeps the binned terms.
+  const bool mesh = sizeof(T) == 8 && g->mesh_w > 0 && g->mesh_w <= 8 && nodes <= ADJ_LDS_N;
   double* plane = nullptr;
-  if (d_w && g->N <= ADJ_LDS_N && planes >= ADJ_MIN_PLANES && Q >= 2 * g->N)
-    plane = (double*)ws_try(ctx, WS_ADJ, sizeof(double) * ADJ_PLANES * g->N);
+  if (d_w && (mesh || g->N <= ADJ_LDS_N) && planes >= ADJ_MIN_PLANES && Q >= 2 * g->N)
+    plane = (double*)ws_try(ctx, WS_ADJ, sizeof(double) * ADJ_PLANES * (mesh ? nodes : g->N));
+  void* tab = nullptr;
+  if (plane && mesh) tab = ws_try(ctx, WS_TMP2, table_bytes<T>(g, true));
+  const int form = tab ? g->mesh_w : 0;
+  const int64_t n = form ? nodes : g->N;
+  if (!tab) RBF_TRY(eval_ws<T>(ctx, g, false, &tab));
+  Nbr<T> nb;
+  RBF_TRY(pack_nbr<T>(ctx, p, g, w, tab, form != 0, false, &nb));
+  const EvalK<T> k = make_consts<T>(p, g, pose, 0.0, form != 0);
+  const auto launch = [&](auto kern, unsigned blocks, int nt, size_t lds, double* out) {
+    kern<<<blocks, nt, lds, ctx->stream>>>((const T*)pts, Q, nb, k, dim == 3 ? dpose : nullptr,
+                                           (const T*)gf, dim == 3 ? (const T*)gr : nullptr,
+                                           (T*)d_pts, out, dim == 3 ? d_pose : nullptr);
+  };
   if (plane) {
-    const size_t lds = sizeof(double) * (size_t)g->N;
-    if (dim == 3)
-      k_eval_adjoint<T, true, true><<<(unsigned)planes, ADJ_NT, lds, ctx->stream>>>(
-          (const T*)pts, Q, tab, g->N, g->d_estart, eg, k, dpose, (const T*)gf, (const T*)gr,
-          (T*)d_pts, plane, d_pose);
-    else
-      k_eval_adjoint<T, false, true><<<(unsigned)planes, ADJ_NT, lds, ctx->stream>>>(
-          (const T*)pts, Q, tab, g->N, g->d_estart, eg, k, nullptr, (const T*)gf, nullptr,
-          (T*)d_pts, plane, nullptr);
+    const size_t lds = sizeof(double) * (size_t)n;
+    const bool p3 = dim == 3;
+    if constexpr (sizeof(T) == 8) {
+      if (form == 4)
+        launch(p3 ? k_eval_adjoint<T, true, true, 4> : k_eval_adjoint<T, false, true, 4>,
+               (unsigned)planes, ADJ_NT, lds, plane);
+      else if (form == 8)
+        launch(p3 ? k_eval_adjoint<T, true, true, 8> : k_eval_adjoint<T, false, true, 8>,
+               (unsigned)planes, ADJ_NT, lds, plane);
+    }
+    if (form == 0)
+      launch(p3 ? k_eval_adjoint<T, true, true, 0> : k_eval_adjoint<T, false, true, 0>,
+             (unsigned)planes, ADJ_NT, lds, plane);
     RBF_LAUNCHED(ctx, "k_eval_adjoint");
-    k_adjoint_sum<<<ceil_div(g->N, 64), 1024, 0, ctx->stream>>>(plane, (int)planes, g->N, d_w);
+    k_adjoint_sum<<<ceil_div(n, 64), 1024, 0, ctx->stream>>>(
+        plane, (int)planes, n, form ? g->d_mesh_map : nullptr, d_w);
     RBF_LAUNCHED(ctx, "k_adjoint_sum");
     return RBF_OK;
   }
-  const unsigned blocks = (unsigned)ceil_div(Q * LPP, 256);
-  if (dim == 3)
-    k_eval_adjoint<T, true, false><<<blocks, 256, 0, ctx->stream>>>(
-        (const T*)pts, Q, tab, g->N, g->d_estart, eg, k, dpose, (const T*)gf, (const T*)gr,
-        (T*)d_pts, d_w, d_pose);
-  else
-    k_eval_adjoint<T, false, false><<<blocks, 256, 0, ctx->stream>>>(
-        (const T*)pts, Q, tab, g->N, g->d_estart, eg, k, nullptr, (const T*)gf, nullptr, (T*)d_pts,
-        d_w, nullptr);
+  launch(dim == 3 ? k_eval_adjoint<T, true, false, 0> : k_eval_adjoint<T, false, false, 0>,
+         (unsigned)ceil_div(Q * LPP, 256), 256, 0, d_w);
   RBF_LAUNCHED(ctx, "k_eval_adjoint");
   return RBF_OK;
 }
