@@ -75,7 +75,7 @@ namespace {
 
 // Byte offsets of one patch's workspace (each part 256-byte aligned).
 struct PatchLayout {
-  size_t vals, cols, nnz, Ut, Vt, S, Lb, LiT, Linv, wpart, glist, gR, gH, vlo, total;
+  size_t vals, cols, nnz, Ut, Vt, S, Lb, LiT, Linv, glist, gR, gH, vlo, total;
 };
 
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
@@ -100,7 +100,6 @@ PatchLayout layout(int64_t N, int32_t kmax, int32_t Bp, bool groups, int64_t Rca
   L.Lb = take(sizeof(double) * (size_t)Bp * Bp);
   L.LiT = take(sizeof(double) * (size_t)Bp * Bp);
   L.Linv = take(sizeof(double) * (size_t)nblk * 64 * 64);
-  L.wpart = take(sizeof(double) * (size_t)nblk * N);
   L.glist = groups ? take(sizeof(int32_t) * (size_t)ng * Rcap) : 0;
   L.gR = groups ? take(sizeof(int32_t) * (size_t)ng) : 0;
   L.gH = groups ? take(sizeof(double) * (size_t)ng * Rcap * 64) : 0;
@@ -205,7 +204,6 @@ static rbf_status batched_build(rbf_batched* b, rbf_ctx* ctx) {
         J.LiT = (double*)(m + L.LiT);
         J.Linv = (double*)(m + L.Linv);
         J.Vt = (double*)(m + L.Vt);
-        J.wpart = (double*)(m + L.wpart);
         if (Rcap[p] > 0) {
           J.glist = (int32_t*)(m + L.glist);
           J.gR = (int32_t*)(m + L.gR);
@@ -236,18 +234,17 @@ static rbf_status batched_build(rbf_batched* b, rbf_ctx* ctx) {
           mx(r.gm_x, ceil_div(J.N, 128));
           mx(r.gm_y, ng);
           mx(r.sg_x, (int64_t)ng * (ng + 1) / 2);
+        } else {
+          mx(r.gu_x, ceil_div(J.N, 1024));
+          mx(r.gu_y, ceil_div(J.Bp, 8));
+          mx(r.s_x, ceil_div(J.Bp, 256));
+          mx(r.s_y, J.Bp);
+          mx(r.zero_x, ceil_div((int64_t)J.Bp * J.Bp, 4096));
         }
-        mx(r.gu_x, ceil_div(J.N, 1024));
-        mx(r.gu_y, ceil_div(J.Bp, 8));
-        mx(r.s_x, ceil_div(J.Bp, 256));
-        mx(r.s_y, J.Bp);
-        mx(r.zero_x, ceil_div((int64_t)J.Bp * J.Bp, 4096));
         nsteps = std::max(nsteps, nblk - 1);
         mx(r.lr_x, nblk - 1);
         mx(r.la_x, ceil_div(J.Bp, LINV_TILE) * ceil_div(J.ncols, LINV_TILE));
-        mx(r.wp_x, ceil_div(J.N, 256));
-        mx(r.wp_y, ceil_div(J.Bc, 64));
-        mx(r.ws_x, ceil_div(J.N, 256));
+        mx(r.w_x, ceil_div(J.N, UPD_W_COLS));
         if (b->gemm_prec == RBF_F32) {
           mx(r.cvt_x, ceil_div((int64_t)J.Bc * J.ldu, 256));
           r.cvt_y = 1;

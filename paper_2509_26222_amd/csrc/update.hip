@@ -107,17 +107,15 @@ __global__ void __launch_bounds__(256) k_upd_rows(const double* __restrict__ xy,
 }
 
 // U^T[b, n] = sum_k vals[b,k] P[cols[b,k], n]  (P symmetric: rows of P).
-// Block: 8 batch rows x 1024 columns; each thread 4 columns. With gR, only
-// the rows of groups the grouped kernels leave (more than
-// GATHER_GROUP_RMAX distinct rows of P).
+// Block: 8 batch rows x 1024 columns; each thread 4 columns. For calls without
+// the grouped data.
 __device__ __forceinline__ void upd_gather_u_body(const double* __restrict__ P, int64_t ldp,
     int64_t N, int32_t Bc, int32_t Bp, const double* __restrict__ vals,
     const int32_t* __restrict__ cols, const int32_t* __restrict__ nnz, double* __restrict__ Ut,
-    int64_t ldu, const int32_t* __restrict__ gR, const int32_t* __restrict__ status, int64_t seq) {
+    int64_t ldu, const int32_t* __restrict__ status, int64_t seq) {
   if (seq_skip(status, seq)) return;
   const int64_t n0 = (int64_t)blockIdx.x * 1024 + threadIdx.x;
   const int b0 = blockIdx.y * 8;
-  if (gR && gR[b0 / 64] <= GATHER_GROUP_RMAX) return;
   for (int r = 0; r < 8; ++r) {
     const int b = b0 + r;
     double acc[4] = {0, 0, 0, 0};
@@ -144,8 +142,8 @@ __device__ __forceinline__ void upd_gather_u_body(const double* __restrict__ P, 
 __global__ void __launch_bounds__(256) k_upd_gather_u(const double* __restrict__ P, int64_t ldp,
     int64_t N, int32_t Bc, int32_t Bp, const double* __restrict__ vals,
     const int32_t* __restrict__ cols, const int32_t* __restrict__ nnz, double* __restrict__ Ut,
-    int64_t ldu, const int32_t* __restrict__ gR, const int32_t* __restrict__ status, int64_t seq) {
-  upd_gather_u_body(P, ldp, N, Bc, Bp, vals, cols, nnz, Ut, ldu, gR, status, seq);
+    int64_t ldu, const int32_t* __restrict__ status, int64_t seq) {
+  upd_gather_u_body(P, ldp, N, Bc, Bp, vals, cols, nnz, Ut, ldu, status, seq);
 }
 
 // Grouped gather, step 1 (one workgroup per group of 64 batch rows): the
@@ -238,8 +236,9 @@ __global__ void __launch_bounds__(GG_NT) k_gather_groups(const double* __restric
 // no entries and get 0.
 __device__ __forceinline__ void gather_mfma_body(const double* __restrict__ P, int64_t ldp,
     int64_t N, const int32_t* __restrict__ glist, const int32_t* __restrict__ gR,
-    const double* __restrict__ gH, int64_t Rcap, double* __restrict__ Ut, int64_t ldu,
-    const int32_t* __restrict__ status, int64_t seq) {
+    const double* __restrict__ gH, int64_t Rcap, double* __restrict__ Ut, int64_t ldu, int32_t Bc,
+    int32_t Bp, const double* __restrict__ vals, const int32_t* __restrict__ cols,
+    const int32_t* __restrict__ nnz, const int32_t* __restrict__ status, int64_t seq) {
   if (seq_skip(status, seq)) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = blockIdx.y;
@@ -247,7 +246,18 @@ __device__ __forceinline__ void gather_mfma_body(const double* __restrict__ P, i
   const int32_t* L = glist + (int64_t)g * Rcap;
   const double* H = gH + (int64_t)g * Rcap * 64;
   const int R4 = gR[g];
-  if (R4 > GATHER_GROUP_RMAX) return;  // left to k_upd_gather_u
+  if (R4 > GATHER_GROUP_RMAX) {  // row by row, as upd_gather_u_body (uniform per workgroup)
+    const int64_t n = (int64_t)blockIdx.x * 128 + (threadIdx.x & 127);
+    if (n >= N) return;
+    for (int b = 64 * g + (threadIdx.x >> 7); b < 64 * g + 64; b += 2) {
+      double s = 0.0;
+      const int nz = b < Bc ? nnz[b] : 0;
+      for (int q = 0; q < nz; ++q)
+        s += vals[(int64_t)q * Bp + b] * P[(int64_t)cols[(int64_t)q * Bp + b] * ldp + n];
+      Ut[(int64_t)b * ldu + n] = s;
+    }
+    return;
+  }
   v4d acc[4][2];
 #pragma unroll
   for (int mi = 0; mi < 4; ++mi)
@@ -317,24 +327,18 @@ __device__ __forceinline__ void gather_mfma_body(const double* __restrict__ P, i
 
 __global__ void __launch_bounds__(256) k_gather_mfma(const double* __restrict__ P, int64_t ldp,
     int64_t N, const int32_t* __restrict__ glist, const int32_t* __restrict__ gR,
-    const double* __restrict__ gH, int64_t Rcap, double* __restrict__ Ut, int64_t ldu,
-    const int32_t* __restrict__ status, int64_t seq) {
-  gather_mfma_body(P, ldp, N, glist, gR, gH, Rcap, Ut, ldu, status, seq);
+    const double* __restrict__ gH, int64_t Rcap, double* __restrict__ Ut, int64_t ldu, int32_t Bc,
+    int32_t Bp, const double* __restrict__ vals, const int32_t* __restrict__ cols,
+    const int32_t* __restrict__ nnz, const int32_t* __restrict__ status, int64_t seq) {
+  gather_mfma_body(P, ldp, N, glist, gR, gH, Rcap, Ut, ldu, Bc, Bp, vals, cols, nnz, status, seq);
 }
 
 // S[a][b] (a >= b) = sum_k vals[a,k] U^T[b, cols[a,k]] + R delta_ab; the
-// padding rows a >= Bc carry the identity. With gR, only the rows a of
-// groups the grouped kernel leaves.
-__device__ __forceinline__ void upd_S_body(const double* __restrict__ vals,
+// padding rows a >= Bc carry the identity.
+__device__ __forceinline__ void upd_S_entry(const double* __restrict__ vals,
     const int32_t* __restrict__ cols, const int32_t* __restrict__ nnz,
     const double* __restrict__ Ut, int64_t ldu, int32_t Bc, int32_t Bp, double R,
-    double* __restrict__ S, const int32_t* __restrict__ gR, const int32_t* __restrict__ status,
-    int64_t seq) {
-  if (seq_skip(status, seq)) return;
-  const int b = blockIdx.y;
-  const int a = blockIdx.x * 256 + threadIdx.x;
-  if (a >= Bp || a < b) return;
-  if (gR && gR[a / 64] <= GATHER_GROUP_RMAX) return;
+    double* __restrict__ S, int a, int b) {
   double s;
   if (a < Bc && b < Bc) {
     s = (a == b) ? R : 0.0;
@@ -347,22 +351,37 @@ __device__ __forceinline__ void upd_S_body(const double* __restrict__ vals,
   S[(int64_t)a * Bp + b] = s;
 }
 
+__device__ __forceinline__ void upd_S_body(const double* __restrict__ vals,
+    const int32_t* __restrict__ cols, const int32_t* __restrict__ nnz,
+    const double* __restrict__ Ut, int64_t ldu, int32_t Bc, int32_t Bp, double R,
+    double* __restrict__ S, const int32_t* __restrict__ status, int64_t seq) {
+  if (seq_skip(status, seq)) return;
+  const int b = blockIdx.y;
+  const int a = blockIdx.x * 256 + threadIdx.x;
+  if (a >= Bp || a < b) return;
+  upd_S_entry(vals, cols, nnz, Ut, ldu, Bc, Bp, R, S, a, b);
+}
+
 __global__ void __launch_bounds__(256) k_upd_S(const double* __restrict__ vals,
     const int32_t* __restrict__ cols, const int32_t* __restrict__ nnz,
     const double* __restrict__ Ut, int64_t ldu, int32_t Bc, int32_t Bp, double R,
-    double* __restrict__ S, const int32_t* __restrict__ gR, const int32_t* __restrict__ status,
-    int64_t seq) {
-  upd_S_body(vals, cols, nnz, Ut, ldu, Bc, Bp, R, S, gR, status, seq);
+    double* __restrict__ S, const int32_t* __restrict__ status, int64_t seq) {
+  upd_S_body(vals, cols, nnz, Ut, ldu, Bc, Bp, R, S, status, seq);
 }
 
 // The same lower triangle of S from the grouped gather's data: workgroup
 // (ga, gb), gb <= ga, computes S[a][b] for the 64 rows a of group ga and the
 // 64 columns b of block gb as sum_r H_ga[r][a] U^T[b][list_ga[r]] on FP64
-// MFMA (wave w: columns 16w..16w+15, all 64 rows).
+// MFMA (wave w: columns 16w..16w+15, all 64 rows). It also clears its two
+// blocks of L^{-1}^T, which start at zero in every batch (they accumulate
+// partial sums): stores beside the loads that this kernel waits for, where a
+// launch of their own took 3 to 5 us.
 __device__ __forceinline__ void upd_S_groups_body(const int32_t* __restrict__ glist,
     const int32_t* __restrict__ gR, const double* __restrict__ gH, int64_t Rcap,
     const double* __restrict__ Ut, int64_t ldu, int32_t Bc, int32_t Bp, double R,
-    double* __restrict__ S, const int32_t* __restrict__ status, int64_t seq) {
+    double* __restrict__ S, double* __restrict__ LiT, const double* __restrict__ vals,
+    const int32_t* __restrict__ cols, const int32_t* __restrict__ nnz,
+    const int32_t* __restrict__ status, int64_t seq) {
   if (seq_skip(status, seq)) return;
   const int t = blockIdx.x;
   int ga = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
@@ -374,7 +393,20 @@ __device__ __forceinline__ void upd_S_groups_body(const int32_t* __restrict__ gl
   const int32_t* L = glist + (int64_t)ga * Rcap;
   const double* H = gH + (int64_t)ga * Rcap * 64;
   const int R4 = gR[ga];
-  if (R4 > GATHER_GROUP_RMAX) return;  // left to k_upd_S (uniform per workgroup)
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const int e = 2 * ((int)threadIdx.x + 256 * u), r = e >> 6, c = e & 63;
+    const double2 zero = make_double2(0.0, 0.0);
+    *reinterpret_cast<double2*>(LiT + (int64_t)(64 * ga + r) * Bp + 64 * gb + c) = zero;
+    if (ga != gb)
+      *reinterpret_cast<double2*>(LiT + (int64_t)(64 * gb + r) * Bp + 64 * ga + c) = zero;
+  }
+  if (R4 > GATHER_GROUP_RMAX) {  // entry by entry, as upd_S_body (uniform per workgroup)
+    const int a = 64 * ga + (threadIdx.x & 63);
+    for (int b = 64 * gb + (threadIdx.x >> 6); b < 64 * gb + 64 && b <= a; b += 4)
+      upd_S_entry(vals, cols, nnz, Ut, ldu, Bc, Bp, R, S, a, b);
+    return;
+  }
   // the group's row list in LDS, so that the value loads of four k-steps
   // can be issued together below (each step's value load needs its index)
   __shared__ int32_t Ls[GATHER_GROUP_RMAX];
@@ -427,8 +459,10 @@ __device__ __forceinline__ void upd_S_groups_body(const int32_t* __restrict__ gl
 __global__ void __launch_bounds__(256) k_upd_S_groups(const int32_t* __restrict__ glist,
     const int32_t* __restrict__ gR, const double* __restrict__ gH, int64_t Rcap,
     const double* __restrict__ Ut, int64_t ldu, int32_t Bc, int32_t Bp, double R,
-    double* __restrict__ S, const int32_t* __restrict__ status, int64_t seq) {
-  upd_S_groups_body(glist, gR, gH, Rcap, Ut, ldu, Bc, Bp, R, S, status, seq);
+    double* __restrict__ S, double* __restrict__ LiT, const double* __restrict__ vals,
+    const int32_t* __restrict__ cols, const int32_t* __restrict__ nnz,
+    const int32_t* __restrict__ status, int64_t seq) {
+  upd_S_groups_body(glist, gR, gH, Rcap, Ut, ldu, Bc, Bp, R, S, LiT, vals, cols, nnz, status, seq);
 }
 
 // ------------------------------------------------------------- 64x64 tiles
@@ -1002,47 +1036,54 @@ __global__ void __launch_bounds__(256) k_trsm_blocks(double* __restrict__ Ut, in
   }
 }
 
-// w[n] += sum_b V^T[b, n] t[b], t = V^T[:, N]; stage 1 sums groups of 64
-// rows into part[g][n], stage 2 adds the groups in order (deterministic).
-__device__ __forceinline__ void upd_w_part_body(const double* __restrict__ Ut, int64_t ldu,
-    int64_t N, int32_t Bc, double* __restrict__ part, const int32_t* __restrict__ status,
-    int64_t seq) {
-  if (seq_skip(status, seq)) return;
-  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
-  const int b0 = blockIdx.y * 64;
-  const int b1 = b0 + 64 < Bc ? b0 + 64 : Bc;
-  double s0 = 0.0, s1 = 0.0;
-  int b = b0;
-  for (; b + 1 < b1; b += 2) {
-    s0 += Ut[(int64_t)b * ldu + n] * Ut[(int64_t)b * ldu + N];
-    s1 += Ut[(int64_t)(b + 1) * ldu + n] * Ut[(int64_t)(b + 1) * ldu + N];
-  }
-  if (b < b1) s0 += Ut[(int64_t)b * ldu + n] * Ut[(int64_t)b * ldu + N];
-  part[(int64_t)blockIdx.y * N + n] = s0 + s1;
-}
+// w[n] += sum_b V^T[b, n] t[b], t = V^T[:, N]: 16 columns per workgroup, row
+// lane r takes the rows r, r + 64, ... with 16 loads in flight (a batch of 1024
+// rows is one round trip), and the lanes' sums are added in a fixed order. Few
+// columns spread over the chip: 1024 rows, N = 400: 6.9 us in one launch (11 + 5
+// with sums of 64 rows, two loads at a time, and a launch to add them; 19 with
+// 64 columns per workgroup).
+constexpr int UPD_W_NT = 1024;
 
-__global__ void __launch_bounds__(256) k_upd_w_part(const double* __restrict__ Ut, int64_t ldu,
-    int64_t N, int32_t Bc, double* __restrict__ part, const int32_t* __restrict__ status,
-    int64_t seq) {
-  upd_w_part_body(Ut, ldu, N, Bc, part, status, seq);
-}
-
-__device__ __forceinline__ void upd_w_sum_body(double* __restrict__ w,
-    const double* __restrict__ part, int64_t N, int32_t ngroups, const int32_t* __restrict__ status,
-    int64_t seq) {
+__device__ __forceinline__ void upd_w_body(double* __restrict__ w, const double* __restrict__ Ut,
+    int64_t ldu, int64_t N, int32_t Bc, const int32_t* __restrict__ status, int64_t seq) {
   if (seq_skip(status, seq)) return;
-  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
+  constexpr int U = 16, W = UPD_W_NT / UPD_W_COLS;
+  __shared__ double part[W][UPD_W_COLS];
+  const int c = threadIdx.x % UPD_W_COLS, r = threadIdx.x / UPD_W_COLS;
+  const int64_t n = (int64_t)blockIdx.x * UPD_W_COLS + c;
+  const int64_t nc = n < N ? n : N - 1;
   double s = 0.0;
-  for (int g = 0; g < ngroups; ++g) s += part[(int64_t)g * N + n];
+  for (int b0 = r; b0 < Bc; b0 += W * U) {
+    double v[U], t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t b = min(b0 + W * u, Bc - 1);
+      v[u] = Ut[b * ldu + nc];
+      t[u] = Ut[b * ldu + N];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (b0 + W * u < Bc) s += v[u] * t[u];
+  }
+  part[r][c] = s;
+  __syncthreads();
+  if (r < 8) {
+#pragma unroll
+    for (int q = 1; q < W / 8; ++q) s += part[r + 8 * q][c];
+  }
+  __syncthreads();
+  if (r < 8) part[r][c] = s;
+  __syncthreads();
+  if (r != 0 || n >= N) return;
+#pragma unroll
+  for (int q = 1; q < 8; ++q) s += part[q][c];
   w[n] += s;
 }
 
-__global__ void __launch_bounds__(256) k_upd_w_sum(double* __restrict__ w,
-    const double* __restrict__ part, int64_t N, int32_t ngroups, const int32_t* __restrict__ status,
-    int64_t seq) {
-  upd_w_sum_body(w, part, N, ngroups, status, seq);
+__global__ void __launch_bounds__(UPD_W_NT) k_upd_w(double* __restrict__ w,
+    const double* __restrict__ Ut, int64_t ldu, int64_t N, int32_t Bc,
+    const int32_t* __restrict__ status, int64_t seq) {
+  upd_w_body(w, Ut, ldu, N, Bc, status, seq);
 }
 
 // Touched row blocks of P: flags[c / SYRK_TILE] = 1 for every center c in
@@ -1089,8 +1130,6 @@ rbf_status update_workspace(rbf_ctx* ctx, int64_t N, int32_t kmax, int64_t Bmax,
   ws->Vt2 = ws->Vt + (size_t)Bp * ldu;
   ws->Linv = (double*)ws_get(ctx, WS_UPD_LINV, sizeof(double) * (size_t)nblk_max * NB * NB, &st);
   if (!ws->Linv) return st;
-  ws->wpart = (double*)ws_get(ctx, WS_TMP3, sizeof(double) * (size_t)nblk_max * N, &st);
-  if (!ws->wpart) return st;
   ws->Rcap = 0;
   ws->glist = nullptr;
   ws->gR = nullptr;
@@ -1312,7 +1351,6 @@ rbf_status update_run(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g,
   double* S = ws.S;
   double* Lb = ws.Lb;
   double* Linv = ws.Linv;
-  double* wpart = ws.wpart;
   const RegKU rk = regku(p);
   const int64_t nb_total = ceil_div(M, B);
   // Launch group (sequence number) of batch bi: seq0 + bi. A failure in
@@ -1370,42 +1408,38 @@ rbf_status update_run(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g,
       RBF_LAUNCHED(ctx, "k_gather_groups");
       dim3 gm((unsigned)ceil_div(N, 128), (unsigned)(Bpc / 64));
       k_gather_mfma<<<gm, 256, 0, ctx->stream>>>(P, ldp, N, ws.glist, ws.gR, ws.gH, ws.Rcap, Ut,
-                                                  ldu, ctx->d_status, sq);
+                                                  ldu, Bc, Bpc, vals, cols, nnz, ctx->d_status,
+                                                  sq);
       RBF_LAUNCHED(ctx, "k_gather_mfma");
-    }
-    {  // all rows without the grouped data, else the groups it leaves
+    } else {
       dim3 gg((unsigned)ceil_div(N, 1024), (unsigned)ceil_div(Bpc, 8));
       k_upd_gather_u<<<gg, 256, 0, ctx->stream>>>(P, ldp, N, Bc, Bpc, vals, cols, nnz, Ut, ldu,
-                                                   ws.gH ? ws.gR : nullptr, ctx->d_status, sq);
+                                                   ctx->d_status, sq);
       RBF_LAUNCHED(ctx, "k_upd_gather_u");
     }
     prof_end(ctx, RBF_PROF_GATHER);
     if (ws.gH) {
       const int ng = Bpc / 64;
       k_upd_S_groups<<<ng * (ng + 1) / 2, 256, 0, ctx->stream>>>(
-          ws.glist, ws.gR, ws.gH, ws.Rcap, Ut, ldu, Bc, Bpc, p->R, S, ctx->d_status, sq);
+          ws.glist, ws.gR, ws.gH, ws.Rcap, Ut, ldu, Bc, Bpc, p->R, S, ws.LiT, vals, cols, nnz,
+          ctx->d_status, sq);
       RBF_LAUNCHED(ctx, "k_upd_S_groups");
-    }
-    {  // all rows without the grouped data, else the groups it leaves
+    } else {
       dim3 gs((unsigned)ceil_div(Bpc, 256), (unsigned)Bpc);
       k_upd_S<<<gs, 256, 0, ctx->stream>>>(vals, cols, nnz, Ut, ldu, Bc, Bpc, p->R, S,
-                                           ws.gH ? ws.gR : nullptr, ctx->d_status, sq);
+                                           ctx->d_status, sq);
       RBF_LAUNCHED(ctx, "k_upd_S");
     }
     double* Vt = VtB[bi & 1];
     prof_begin(ctx, RBF_PROF_CHOL);
-    RBF_TRY(fill_zero(ctx, ws.LiT, sizeof(double) * (size_t)Bpc * Bpc));
+    if (!ws.gH) RBF_TRY(fill_zero(ctx, ws.LiT, sizeof(double) * (size_t)Bpc * Bpc));
     RBF_TRY(chol_blocked(ctx, S, Bpc, Lb, Linv, ctx->index_base + bi, sq, ws.LiT, gemm_prec));
     prof_end(ctx, RBF_PROF_CHOL);
     prof_begin(ctx, RBF_PROF_TRSM);
     RBF_TRY(linv_apply(ctx, ws.LiT, Bpc, Ut, ldu, N + 1, Vt, sq));
     prof_end(ctx, RBF_PROF_TRSM);
-    dim3 gw((unsigned)ceil_div(N, 256), (unsigned)ceil_div(Bc, 64));
-    k_upd_w_part<<<gw, 256, 0, ctx->stream>>>(Vt, ldu, N, Bc, wpart, ctx->d_status, sq);
-    RBF_LAUNCHED(ctx, "k_upd_w_part");
-    k_upd_w_sum<<<ceil_div(N, 256), 256, 0, ctx->stream>>>(w, wpart, N, (int32_t)gw.y,
-                                                           ctx->d_status, sq);
-    RBF_LAUNCHED(ctx, "k_upd_w_sum");
+    k_upd_w<<<ceil_div(N, UPD_W_COLS), UPD_W_NT, 0, ctx->stream>>>(w, Vt, ldu, N, Bc, ctx->d_status, sq);
+    RBF_LAUNCHED(ctx, "k_upd_w");
     return RBF_OK;
   };
   // whatever path leaves this function, `ms` ends up ordered after `as`
@@ -1518,32 +1552,33 @@ __global__ void __launch_bounds__(GG_NT) k_gather_groups_g(const GJob* __restric
 __global__ void __launch_bounds__(256) k_gather_mfma_g(const GJob* __restrict__ jobs) {
   const GJob& J = jobs[blockIdx.z];
   if (!J.gH || (int64_t)blockIdx.x * 128 >= J.N || (int32_t)blockIdx.y >= J.Bp / 64) return;
-  gather_mfma_body(J.P, J.ldp, J.N, J.glist, J.gR, J.gH, J.Rcap, J.Ut, J.ldu, J.status, J.seq);
+  gather_mfma_body(J.P, J.ldp, J.N, J.glist, J.gR, J.gH, J.Rcap, J.Ut, J.ldu, J.Bc, J.Bp, J.vals,
+                   J.cols, J.nnz, J.status, J.seq);
 }
 
 __global__ void __launch_bounds__(256) k_upd_gather_u_g(const GJob* __restrict__ jobs) {
   const GJob& J = jobs[blockIdx.z];
-  if ((int64_t)blockIdx.x * 1024 >= J.N || (int32_t)blockIdx.y * 8 >= J.Bp) return;
-  upd_gather_u_body(J.P, J.ldp, J.N, J.Bc, J.Bp, J.vals, J.cols, J.nnz, J.Ut, J.ldu,
-                    J.gH ? J.gR : nullptr, J.status, J.seq);
+  if (J.gH || (int64_t)blockIdx.x * 1024 >= J.N || (int32_t)blockIdx.y * 8 >= J.Bp) return;
+  upd_gather_u_body(J.P, J.ldp, J.N, J.Bc, J.Bp, J.vals, J.cols, J.nnz, J.Ut, J.ldu, J.status,
+                    J.seq);
 }
 
 __global__ void __launch_bounds__(256) k_upd_S_groups_g(const GJob* __restrict__ jobs) {
   const GJob& J = jobs[blockIdx.z];
   const int32_t ng = J.Bp / 64;
   if (!J.gH || (int32_t)blockIdx.x >= ng * (ng + 1) / 2) return;
-  upd_S_groups_body(J.glist, J.gR, J.gH, J.Rcap, J.Ut, J.ldu, J.Bc, J.Bp, J.R, J.S,
-                    J.status, J.seq);
+  upd_S_groups_body(J.glist, J.gR, J.gH, J.Rcap, J.Ut, J.ldu, J.Bc, J.Bp, J.R, J.S, J.LiT,
+                    J.vals, J.cols, J.nnz, J.status, J.seq);
 }
 
 __global__ void __launch_bounds__(256) k_upd_S_g(const GJob* __restrict__ jobs) {
   const GJob& J = jobs[blockIdx.z];
-  if ((int32_t)blockIdx.x * 256 >= J.Bp || (int32_t)blockIdx.y >= J.Bp) return;
-  upd_S_body(J.vals, J.cols, J.nnz, J.Ut, J.ldu, J.Bc, J.Bp, J.R, J.S, J.gH ? J.gR : nullptr,
-             J.status, J.seq);
+  if (J.gH || (int32_t)blockIdx.x * 256 >= J.Bp || (int32_t)blockIdx.y >= J.Bp) return;
+  upd_S_body(J.vals, J.cols, J.nnz, J.Ut, J.ldu, J.Bc, J.Bp, J.R, J.S, J.status, J.seq);
 }
 
-// L^{-1}^T starts at zero in every batch (its blocks accumulate partial sums).
+// L^{-1}^T starts at zero in every batch (its blocks accumulate partial sums):
+// for jobs without the grouped data, whose kernel clears it.
 __global__ void __launch_bounds__(256) k_zero_lit_g(const GJob* __restrict__ jobs) {
   const GJob& J = jobs[blockIdx.z];
   const int64_t n = (int64_t)J.Bp * J.Bp;
@@ -1676,15 +1711,10 @@ __global__ void __launch_bounds__(256) k_linv_row_g(const GJob* __restrict__ job
   linv_row_body(J.Bp, nblk - 1, J.Lb, J.Linv, J.LiT, J.status, J.seq);
 }
 
-__global__ void __launch_bounds__(256) k_upd_w_part_g(const GJob* __restrict__ jobs) {
+__global__ void __launch_bounds__(UPD_W_NT) k_upd_w_g(const GJob* __restrict__ jobs) {
   const GJob& J = jobs[blockIdx.z];
-  if ((int32_t)blockIdx.y * 64 >= J.Bc) return;  // columns beyond N return in the body
-  upd_w_part_body(J.Vt, J.ldu, J.N, J.Bc, J.wpart, J.status, J.seq);
-}
-
-__global__ void __launch_bounds__(256) k_upd_w_sum_g(const GJob* __restrict__ jobs) {
-  const GJob& J = jobs[blockIdx.z];
-  upd_w_sum_body(J.w, J.wpart, J.N, (J.Bc + 63) / 64, J.status, J.seq);
+  if ((int64_t)blockIdx.x * UPD_W_COLS >= J.N) return;
+  upd_w_body(J.w, J.Vt, J.ldu, J.N, J.Bc, J.status, J.seq);
 }
 
 template <bool PHASED>
@@ -1692,8 +1722,10 @@ static rbf_status chol_grouped_t(rbf_ctx* ctx, const GRound& r) {
   if (r.n <= 0) return RBF_OK;
   const unsigned nz = (unsigned)r.n;
   hipStream_t s = ctx->stream;
-  k_zero_lit_g<<<dim3(r.zero_x, 1, nz), 256, 0, s>>>(r.jobs);
-  RBF_LAUNCHED(ctx, "k_zero_lit_g");
+  if (r.zero_x > 0) {
+    k_zero_lit_g<<<dim3(r.zero_x, 1, nz), 256, 0, s>>>(r.jobs);
+    RBF_LAUNCHED(ctx, "k_zero_lit_g");
+  }
   k_chol_first_g<PHASED><<<dim3(1, 1, nz), 256, 0, s>>>(r.jobs);
   RBF_LAUNCHED(ctx, "k_chol_first_g");
   for (int32_t kb = 0; kb < r.nsteps; ++kb) {
@@ -1731,20 +1763,22 @@ rbf_status update_round_grouped(rbf_ctx* ctx, const GRound& r, rbf_prec prec) {
     k_gather_mfma_g<<<dim3(r.gm_x, r.gm_y, nz), 256, 0, s>>>(r.jobs);
     RBF_LAUNCHED(ctx, "k_gather_mfma_g");
   }
-  k_upd_gather_u_g<<<dim3(r.gu_x, r.gu_y, nz), 256, 0, s>>>(r.jobs);
-  RBF_LAUNCHED(ctx, "k_upd_gather_u_g");
+  if (r.gu_x > 0) {
+    k_upd_gather_u_g<<<dim3(r.gu_x, r.gu_y, nz), 256, 0, s>>>(r.jobs);
+    RBF_LAUNCHED(ctx, "k_upd_gather_u_g");
+  }
   if (r.sg_x > 0) {
     k_upd_S_groups_g<<<dim3(r.sg_x, 1, nz), 256, 0, s>>>(r.jobs);
     RBF_LAUNCHED(ctx, "k_upd_S_groups_g");
   }
-  k_upd_S_g<<<dim3(r.s_x, r.s_y, nz), 256, 0, s>>>(r.jobs);
-  RBF_LAUNCHED(ctx, "k_upd_S_g");
+  if (r.s_x > 0) {
+    k_upd_S_g<<<dim3(r.s_x, r.s_y, nz), 256, 0, s>>>(r.jobs);
+    RBF_LAUNCHED(ctx, "k_upd_S_g");
+  }
   RBF_TRY(chol_grouped(ctx, r, prec));
   RBF_TRY(linv_apply_grouped(ctx, r));
-  k_upd_w_part_g<<<dim3(r.wp_x, r.wp_y, nz), 256, 0, s>>>(r.jobs);
-  RBF_LAUNCHED(ctx, "k_upd_w_part_g");
-  k_upd_w_sum_g<<<dim3(r.ws_x, 1, nz), 256, 0, s>>>(r.jobs);
-  RBF_LAUNCHED(ctx, "k_upd_w_sum_g");
+  k_upd_w_g<<<dim3(r.w_x, 1, nz), UPD_W_NT, 0, s>>>(r.jobs);
+  RBF_LAUNCHED(ctx, "k_upd_w_g");
   return syrk_grouped(ctx, r, prec);
 }
 

@@ -65,7 +65,6 @@ struct UpdWs {
   double* S;
   double* Lb;
   double* Linv;
-  double* wpart;
   // gather by groups of 64 batch rows (when N <= GATHER_GROUP_NMAX): per
   // group the distinct rows of P its points touch (glist, Rcap entries),
   // their count rounded up to 4 (gR), and the dense block of H over those
@@ -96,6 +95,7 @@ constexpr int64_t GATHER_GROUP_NMAX = (int64_t)1 << 17;
 // kernels instead of the dense group products, whose work grows with the
 // number of distinct rows.
 constexpr int32_t GATHER_GROUP_RMAX = 512;
+constexpr int UPD_W_COLS = 16;  // columns per workgroup of the weight kernel
 rbf_status update_workspace(rbf_ctx* ctx, int64_t N, int32_t kmax, int64_t Bmax,
                             rbf_prec gemm_prec, UpdWs* ws);
 
@@ -186,7 +186,6 @@ struct GJob {
   double* LiT;
   double* Linv;
   double* Vt;
-  double* wpart;
   int32_t* glist;  // null: no grouped gather for this patch
   int32_t* gR;
   double* gH;
@@ -209,7 +208,7 @@ struct GRound {
   size_t gg_lds;
   int32_t nsteps;                 // Cholesky step launches (largest nblk - 1)
   const int32_t* step_x;          // host: workgroups of step kb, kb < nsteps
-  int32_t lr_x, la_x, wp_x, wp_y, ws_x, cvt_x, cvt_y;
+  int32_t lr_x, la_x, w_x, cvt_x, cvt_y;
   const int64_t* pre_main;        // device: prefix of 128x128-tile workgroups
   const int64_t* pre_tail;        // device: prefix of sub-tile workgroups
   int64_t n_main, n_tail;         // total workgroups of each
