@@ -242,23 +242,30 @@ __device__ __forceinline__ void syrk_f64_body(double* __restrict__ P, int64_t ld
   direct_syrk<BM, BN>(P, ldp, N, Ut, ldu, K, i0, j0, strip[wave]);
 }
 
-// Main part: whole rounds of tiles in blocks of 64x32, two waves per SIMD.
+// Main part: whole rounds of tiles in blocks of 64x32, two waves per SIMD, and
+// behind them, in the same launch, the tiles past the last whole round in the
+// tail's blocks: they start as the main part's workgroups end. N = 10,000, K =
+// 1024: 1534 + 73 -> 1582 us.
 __global__ void __launch_bounds__(256, 2) k_syrk_f64(double* __restrict__ P, int64_t ldp,
     int64_t N, const double* __restrict__ Ut, int64_t ldu, int32_t K, int64_t T, int64_t per_xcd,
     int64_t main_per_xcd, const int32_t* __restrict__ flags, int part,
     const int32_t* __restrict__ status, int64_t seq) {
-  syrk_f64_body<4, 2>(P, ldp, N, Ut, ldu, K, T, per_xcd, 0, main_per_xcd, flags, part, status,
-                      seq, blockIdx.x);
+  const int64_t main = main_per_xcd * 8 * SYRK_MAIN_WG;
+  if ((int64_t)blockIdx.x < main)
+    syrk_f64_body<4, 2>(P, ldp, N, Ut, ldu, K, T, per_xcd, 0, main_per_xcd, flags, part, status,
+                        seq, blockIdx.x);
+  else
+    syrk_f64_body<2, 2>(P, ldp, N, Ut, ldu, K, T, per_xcd, main_per_xcd, per_xcd, flags, part,
+                        status, seq, blockIdx.x - main);
 }
 
-// Tail: the tiles past the last whole round, in blocks of 32x32, which spread
-// the leftover work over the chip.
+// Products with less than one whole round of tiles: blocks of 32x32, which
+// spread the work over the chip.
 __global__ void __launch_bounds__(256, 3) k_syrk_f64_tail(double* __restrict__ P, int64_t ldp,
     int64_t N, const double* __restrict__ Ut, int64_t ldu, int32_t K, int64_t T, int64_t per_xcd,
-    int64_t main_per_xcd, const int32_t* __restrict__ flags, int part,
-    const int32_t* __restrict__ status, int64_t seq) {
-  syrk_f64_body<2, 2>(P, ldp, N, Ut, ldu, K, T, per_xcd, main_per_xcd, per_xcd, flags, part,
-                      status, seq, blockIdx.x);
+    const int32_t* __restrict__ flags, int part, const int32_t* __restrict__ status, int64_t seq) {
+  syrk_f64_body<2, 2>(P, ldp, N, Ut, ldu, K, T, per_xcd, 0, per_xcd, flags, part, status, seq,
+                      blockIdx.x);
 }
 
 // Small products: lower 32x32 tiles in row order, one workgroup of four 16x16
@@ -719,16 +726,14 @@ rbf_status syrk_update(rbf_ctx* ctx, double* P, int64_t ldp, int64_t N, const do
       prof_end(ctx, RBF_PROF_SYRK);
       return RBF_OK;
     }
+    const int64_t tail = (per_xcd - main_per_xcd) * 8 * SYRK_SUB_PER_TILE;
     if (main_per_xcd > 0) {
-      k_syrk_f64<<<(unsigned)(main_per_xcd * 8 * SYRK_MAIN_WG), 256, 0, ctx->stream>>>(
+      k_syrk_f64<<<(unsigned)(main_per_xcd * 8 * SYRK_MAIN_WG + tail), 256, 0, ctx->stream>>>(
           P, ldp, N, Ut, ldu, Bc, T, per_xcd, main_per_xcd, flags, part, ctx->d_status, seq);
       RBF_LAUNCHED(ctx, "k_syrk_f64");
-    }
-    if (main_per_xcd < per_xcd) {
-      const unsigned gt = (unsigned)((per_xcd - main_per_xcd) * 8 * SYRK_SUB_PER_TILE);
-      k_syrk_f64_tail<<<gt, 256, 0, ctx->stream>>>(P, ldp, N, Ut, ldu, Bc, T, per_xcd,
-                                                   main_per_xcd, flags, part, ctx->d_status,
-                                                   seq);
+    } else if (tail > 0) {
+      k_syrk_f64_tail<<<(unsigned)tail, 256, 0, ctx->stream>>>(P, ldp, N, Ut, ldu, Bc, T, per_xcd,
+                                                               flags, part, ctx->d_status, seq);
       RBF_LAUNCHED(ctx, "k_syrk_f64_tail");
     }
     prof_end(ctx, RBF_PROF_SYRK);
