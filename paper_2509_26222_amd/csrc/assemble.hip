@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(256) k_gram_fill(const double* __restrict__ cx
 // the order of the bins. Each regressor value is formed once per point and
 // candidate; the row-wise kernel below forms the 28 values of a point again
 // for every one of the 28 rows it belongs to, two passes per row. 800,000
-// points on 40,000 centers: 10.4 -> 0.70 ms; 10,007 on 5,041: 224 -> 53 us.
+// points on 40,000 centers: 10.4 -> 0.95 ms; 10,007 on 5,041: 224 -> 53 us.
 // What bounds it now is the FP64 exponentials of the candidates (81 formed
 // for 28 in the support).
 //
