@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(256) k_gram_fill(const double* __restrict__ cx
 // the order of the bins. Each regressor value is formed once per point and
 // candidate; the row-wise kernel below forms the 28 values of a point again
 // for every one of the 28 rows it belongs to, two passes per row. 800,000
-// points on 40,000 centers: 10.4 -> 0.95 ms; 10,007 on 5,041: 224 -> 53 us.
+// points on 40,000 centers: 10.4 -> 0.85 ms; 10,007 on 5,041: 224 -> 53 us.
 // What bounds it now is the FP64 exponentials of the candidates (81 formed
 // for 28 in the support).
 //
@@ -232,6 +232,7 @@ __global__ void __launch_bounds__(GRAM_NT) k_gram_bins(
     cy[e] = cxy[2 * s + 1];
   }
   const int nb = (R + 15) / 16, Rp = 16 * nb, nblk = nb * (nb + 1) / 2;
+  const int kk0 = tid / Rp, e0 = tid % Rp, dk = GRAM_NT / Rp, de = GRAM_NT % Rp;
   double* Gb = G + (int64_t)blockIdx.x * ld * ld;
   for (int pass = 0; pass * GRAM_BLK * 8 < nblk; ++pass) {
     int bi[GRAM_BLK], bj[GRAM_BLK];
@@ -248,27 +249,44 @@ __global__ void __launch_bounds__(GRAM_NT) k_gram_bins(
       if (idx < nblk) nq = q + 1;
     }
     double bsum = 0.0;
+    // a chunk's points are loaded while the chunk before is multiplied
+    double nx = 0.0, ny = 0.0, nz = 0.0;
+    auto fetch = [&](int c0) {
+      if (tid < min(GRAM_PTS, np - c0)) {
+        const int64_t p = p0 + c0 + tid;
+        nx = pxy[2 * p];
+        ny = pxy[2 * p + 1];
+        nz = pz[p];
+      }
+    };
+    fetch(0);
     for (int c0 = 0; c0 < np; c0 += GRAM_PTS) {
       const int cnt = min(GRAM_PTS, np - c0);
       __syncthreads();  // the chunk before is read (and, first, cx / cy written)
       if (tid < cnt) {
-        const int64_t p = p0 + c0 + tid;
-        px[tid] = pxy[2 * p];
-        py[tid] = pxy[2 * p + 1];
-        pzs[tid] = pz[p];
+        px[tid] = nx;
+        py[tid] = ny;
+        pzs[tid] = nz;
       }
       __syncthreads();
       const int cnt4 = (cnt + 3) & ~3;
-      for (int kk = wave; kk < cnt4; kk += 8)
-        for (int e = lane; e < Rp; e += 64) {
-          double m = 0.0;
-          if (kk < cnt && e < R) {
-            const double d2 = sq_d(px[kk], py[kk], cx[e], cy[e]);
-            if (d2 <= k.rc2) m = reg_val(d2, k);
-          }
-          Phi[kk][e] = m;
+      // all lanes take entries of the cnt4 x Rp block, row by row
+      for (int kk = kk0, e = e0; kk < cnt4;) {
+        double m = 0.0;
+        if (kk < cnt && e < R) {
+          const double d2 = sq_d(px[kk], py[kk], cx[e], cy[e]);
+          if (d2 <= k.rc2) m = reg_val(d2, k);
         }
+        Phi[kk][e] = m;
+        kk += dk;
+        e += de;
+        if (e >= Rp) {
+          e -= Rp;
+          ++kk;
+        }
+      }
       __syncthreads();
+      if (c0 + GRAM_PTS < np) fetch(c0 + GRAM_PTS);
       for (int kk = 0; kk < cnt4; kk += 4) {
 #pragma unroll
         for (int q = 0; q < GRAM_BLK; ++q)
@@ -277,11 +295,16 @@ __global__ void __launch_bounds__(GRAM_NT) k_gram_bins(
                                                           Phi[kk + kq][16 * bj[q] + li], acc[q],
                                                           0, 0, 0);
       }
-      if (pass == 0 && tid < R)
-        for (int kk = 0; kk < cnt; ++kk) {
-          const double m = Phi[kk][tid];
-          if (m != 0.0) bsum += m * pzs[kk];  // a non-finite height stays with its support
+      if (pass == 0 && tid < R) {
+        for (int kk = 0; kk < cnt; kk += 8) {
+          double m[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) m[u] = Phi[min(kk + u, cnt - 1)][tid];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)  // a non-finite height stays with its support
+            if (kk + u < cnt && m[u] != 0.0) bsum += m[u] * pzs[kk + u];
         }
+      }
     }
     if (pass == 0 && tid < R) B[(int64_t)blockIdx.x * ld + tid] = bsum;
 #pragma unroll
