@@ -588,9 +588,10 @@ typedef struct rbf_batched rbf_batched;
  * products always use 128x128 tiles). */
 enum {
   RBF_TILE_AUTO = 0, /* per patch: whole rounds of 128x128 tiles, the rest as
-                        32x64 sub-tiles (the rule of rbf_update)            */
-  RBF_TILE_128 = 1,  /* 128x128 tiles, 8 waves each                         */
-  RBF_TILE_SUB = 2   /* every tile as 32x64 sub-tiles (more, shorter groups) */
+                        sub-tiles (the rule of rbf_update)                  */
+  RBF_TILE_128 = 1,  /* 128x128 tiles (FP64: two workgroups each)           */
+  RBF_TILE_SUB = 2   /* every tile as sub-tiles (more, shorter workgroups;
+                        FP64: four of 64x64 per tile)                       */
 };
 
 /* Plan the recursive update (as rbf_update, eqs. kf_w_update and
