@@ -543,8 +543,9 @@ rbf_status rbf_assemble_gram(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* 
   // The blocks are read per entry of calH whatever the number of points, the
   // row-wise kernel pays per point: 40,000 centers and 20,000 points 390 us by
   // blocks (the whole call) against 364 row-wise, 40,000 points 400 against
-  // 630; 4,900 centers and 2,450 points 117 against 107.
-  if (ld <= GRAM_RMAX && 4 * M >= 3 * N)
+  // 630; 4,900 centers and 2,450 points 117 against 107. More bins than centers
+  // (scattered ones) are mostly empty blocks.
+  if (ld <= GRAM_RMAX && 4 * M >= 3 * N && nbins <= N)
     ws = (char*)ws_try(ctx, WS_GRAM, (size_t)(strip * blk));
   if (!ws) {  // or no room for the blocks
     k_gram_values<<<ceil_div(N, 4), 256, 0, ctx->stream>>>(

@@ -1018,7 +1018,9 @@ __device__ inline void adjoint_point_mesh(T xr, T yr, int part, const MeshReader
       const T pm = in ? w[q] * ey : (T)0;
       cs[q] += pm;
       cy[q] += pm * dy;
-      if (scatter && in) atomicAdd(&hw[node + q * LPP + r * m.pw], (double)(a * (ex[q] * ey)));
+      const T e = ex[q] * ey;
+      if (scatter && in && e != (T)0)
+        atomicAdd(&hw[node + q * LPP + r * m.pw], (double)(a * e));
     }
   }
   T sx_ = 0, sy_ = 0;
@@ -1500,7 +1502,8 @@ static rbf_status gn_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g, con
   if (g->mesh_w <= 8 && (int64_t)g->mpw * g->mph <= GN_LDS_NODES &&
       (sizeof(T) == 4 || Q <= MESH_WGS * GN_LDS_NT) && mesh_lds<T>(p, g, w, mesh, &mt)) {
     rbf_status st;
-    double* part = (double*)ws_get(ctx, WS_TMP3, sizeof(double) * GN_TERMS * MESH_WGS, &st);
+    const int64_t wgs = ceil_div(Q, mesh_share(Q));
+    double* part = (double*)ws_get(ctx, WS_TMP3, sizeof(double) * GN_TERMS * (size_t)wgs, &st);
     if (!part) return st;
     switch (g->mesh_w) {
       case 4: launch_gn_lds<T, 4>(ctx, pts, Q, mt, k, part); break;
@@ -1508,7 +1511,7 @@ static rbf_status gn_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g, con
     }
     RBF_LAUNCHED(ctx, "k_gn_lds");
     k_eval_gn_sum<<<GN_TERMS, GN_SUM_T, 0, ctx->stream>>>(
-        part, ceil_div(Q, mesh_share(Q)), JtJ, Jtr, rtr);
+        part, wgs, JtJ, Jtr, rtr);
     RBF_LAUNCHED(ctx, "k_eval_gn_sum");
     return RBF_OK;
   }
@@ -1553,14 +1556,13 @@ static rbf_status adjoint_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g
   // window do not fit 1024 threads) also by the mesh form: 200,000 points on
   // 10,000 centers 40 -> 31 us. FP32 keeps the binned terms.
   const bool mesh = sizeof(T) == 8 && g->mesh_w > 0 && g->mesh_w <= 8 && nodes <= ADJ_LDS_N;
-  double* plane = nullptr;
-  if (d_w && (mesh || g->N <= ADJ_LDS_N) && planes >= ADJ_MIN_PLANES && Q >= 2 * g->N)
-    plane = (double*)ws_try(ctx, WS_ADJ, sizeof(double) * ADJ_PLANES * (mesh ? nodes : g->N));
-  void* tab = nullptr;
-  if (plane && mesh) tab = ws_try(ctx, WS_TMP2, table_bytes<T>(g, true));
-  const int form = tab ? g->mesh_w : 0;
-  const int64_t n = form ? nodes : g->N;
-  if (!tab) RBF_TRY(eval_ws<T>(ctx, g, false, &tab));
+  const int64_t n = mesh ? nodes : g->N;
+  double* plane = nullptr;  // the planes, and behind them the mesh form's node weights
+  if (d_w && n <= ADJ_LDS_N && planes >= ADJ_MIN_PLANES && Q >= 2 * g->N)
+    plane = (double*)ws_try(ctx, WS_ADJ, sizeof(double) * (ADJ_PLANES + 1) * n);
+  const int form = plane && mesh ? g->mesh_w : 0;
+  void* tab = plane ? plane + ADJ_PLANES * n : nullptr;
+  if (!form) RBF_TRY(eval_ws<T>(ctx, g, false, &tab));
   Nbr<T> nb;
   RBF_TRY(pack_nbr<T>(ctx, p, g, w, tab, form != 0, false, &nb));
   const EvalK<T> k = make_consts<T>(p, g, pose, 0.0, form != 0);

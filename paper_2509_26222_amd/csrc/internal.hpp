@@ -46,7 +46,8 @@ enum WsSlot {
   WS_SOLVE7,    // solve: L^{-1} of every diagonal block, transposed
   WS_SOLVE8,    // solve: one s x s block, and the second sweep vector
   WS_GRAM,      // assembly: dense blocks of the points' bins
-  WS_ADJ,       // adjoint: planes of dL/dw
+  WS_ADJ,       // adjoint: planes of dL/dw, node weights
+  WS_SELECT,    // center selection: planes of counts
   WS_COUNT
 };
 

@@ -257,7 +257,7 @@ static rbf_status count_nodes(rbf_ctx* ctx, const double* xy, int64_t M, const M
     const int wg = (int)std::max<int64_t>(1, std::min<int64_t>(RADIUS_LDS_WG, M / 256));
     int32_t* part = cnt;
     if (wg > 1) {
-      part = (int32_t*)ws_get(ctx, WS_TMP1, sizeof(int32_t) * nc * wg, &st);
+      part = (int32_t*)ws_get(ctx, WS_SELECT, sizeof(int32_t) * nc * wg, &st);
       if (!part) return st;
     }
     k_radius_lds<<<wg, 1024, sizeof(int32_t) * nc, ctx->stream>>>(xy, M, m, reach, r_kd * r_kd,

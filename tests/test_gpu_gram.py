@@ -1,7 +1,8 @@
 """The information matrix by dense blocks of the points' bins, on both sides
 of its rules: up to 128 and up to 256 candidates per bin (one and several
 passes over a bin's blocks), more than that (the row-wise kernel), more bins
-than one strip holds, fewer points than three for four centers, bins without points, points off the grid, a non-finite
+than one strip holds, fewer points than three for four centers, more bins than
+centers, bins without points, points off the grid, a non-finite
 height.
 
 Tolerance: an entry is a sum of n_p positive products of two regressor values,
@@ -66,6 +67,15 @@ def test_strips_and_empty_bins(ctx, m):
     grid = check(ctx, p, c, xy, rng.normal(size=m))
     ld = (grid.max_candidates + 15) // 16 * 16
     assert grid.nbx * grid.nby * 8 * ld * ld > 128 << 20
+
+
+def test_scattered_centers(ctx):
+    """More bins than centers: the row-wise kernel, however many the points."""
+    rng = np.random.default_rng(11)
+    c = np.concatenate([rng.uniform(0.0, 6.0, size=(60, 2)), [[3000.0, 2000.0]]])
+    xy = rng.uniform(0.0, 6.0, size=(500, 2))
+    grid = check(ctx, api.Params(), c, xy, rng.normal(size=500))
+    assert grid.nbx * grid.nby > c.shape[0]
 
 
 def test_accumulates_and_non_finite_height(ctx):
