@@ -970,10 +970,13 @@ __global__ void __launch_bounds__(GN_LDS_NT) k_gn_lds(
 // in a plane of its own, which k_adjoint_sum adds up. Else every addition is a
 // device atomic, and these bound the kernel (5.6 million of them at 200,000
 // points). 200,000 FP64 points, 10,000 centers: 192 us with device atomics,
-// 40 + 7 us with planes (31 + 7 by the mesh form), bound by the FP64
+// 40 + 7 us with planes (30 + 7 by the mesh form), bound by the FP64
 // exponentials of the candidates and the LDS additions.
 constexpr int64_t ADJ_PLANES = 256;            // one workgroup per CU
-constexpr int ADJ_NT = 1024;                   // its threads (four waves per SIMD)
+// Its threads: four waves per SIMD; three for the mesh form's 8-node windows,
+// whose FP64 registers do not fit four (200,000 points 42.6 -> 40.6 us).
+template <int MW>
+constexpr int adj_threads() { return MW == 8 ? 768 : 1024; }
 constexpr int64_t ADJ_LDS_N = 18 * 1024;       // 144 KB of sums
 constexpr int64_t ADJ_MIN_PLANES = 16;         // 256 points each
 
@@ -1035,12 +1038,12 @@ __device__ inline void adjoint_point_mesh(T xr, T yr, int part, const MeshReader
 
 // MW: 0, the binned form, or (PLANES) the mesh form's window.
 template <typename T, bool POSE, bool PLANES, int MW>
-__global__ void __launch_bounds__(PLANES ? ADJ_NT : 256) k_eval_adjoint(
+__global__ void __launch_bounds__((PLANES ? adj_threads<MW>() : 256)) k_eval_adjoint(
     const T* __restrict__ pts, int64_t Q, Nbr<T> nb, EvalK<T> k0,
     const double* __restrict__ dpose,
     const T* __restrict__ gbar_f, const T* __restrict__ gbar_r, T* __restrict__ d_pts,
     double* __restrict__ d_w, double* __restrict__ d_pose) {
-  constexpr int NT = PLANES ? ADJ_NT : 256, PPB = NT / LPP;
+  constexpr int NT = PLANES ? adj_threads<MW>() : 256, PPB = NT / LPP;
   extern __shared__ double hw[];  // PLANES: this workgroup's dL/dw
   const int64_t N = nb.n;
   const int part = threadIdx.x % LPP;
@@ -1554,7 +1557,7 @@ static rbf_status adjoint_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g
   const int64_t nodes = (int64_t)g->mpw * g->mph;
   // In FP64 on a mesh with windows of up to 8 nodes (the registers of a 12-node
   // window do not fit 1024 threads) also by the mesh form: 200,000 points on
-  // 10,000 centers 40 -> 31 us. FP32 keeps the binned terms.
+  // 10,000 centers 40 -> 30 us. FP32 keeps the binned terms.
   const bool mesh = sizeof(T) == 8 && g->mesh_w > 0 && g->mesh_w <= 8 && nodes <= ADJ_LDS_N;
   const int64_t n = mesh ? nodes : g->N;
   double* plane = nullptr;  // the planes, and behind them the mesh form's node weights
@@ -1577,14 +1580,14 @@ static rbf_status adjoint_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g
     if constexpr (sizeof(T) == 8) {
       if (form == 4)
         launch(p3 ? k_eval_adjoint<T, true, true, 4> : k_eval_adjoint<T, false, true, 4>,
-               (unsigned)planes, ADJ_NT, lds, plane);
+               (unsigned)planes, adj_threads<4>(), lds, plane);
       else if (form == 8)
         launch(p3 ? k_eval_adjoint<T, true, true, 8> : k_eval_adjoint<T, false, true, 8>,
-               (unsigned)planes, ADJ_NT, lds, plane);
+               (unsigned)planes, adj_threads<8>(), lds, plane);
     }
     if (form == 0)
       launch(p3 ? k_eval_adjoint<T, true, true, 0> : k_eval_adjoint<T, false, true, 0>,
-             (unsigned)planes, ADJ_NT, lds, plane);
+             (unsigned)planes, adj_threads<0>(), lds, plane);
     RBF_LAUNCHED(ctx, "k_eval_adjoint");
     k_adjoint_sum<<<ceil_div(n, 64), 1024, 0, ctx->stream>>>(
         plane, (int)planes, n, form ? g->d_mesh_map : nullptr, d_w);
