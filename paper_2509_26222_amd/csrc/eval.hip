@@ -899,17 +899,15 @@ __global__ void __launch_bounds__(GN_SUM_T) k_eval_gn_sum(const double* __restri
 
 // Mesh form with the node weights in LDS, one lane per point: the lane adds its
 // point's 28 products itself (the quad's lanes each formed J and took turns
-// with 7). Fixed orders throughout: a lane's points, eight lanes to a run, the
-// runs of a term.
+// with 7). Fixed orders throughout: a lane's points, the lanes of a term.
 constexpr int GN_LDS_NT = 512;
-constexpr int64_t GN_LDS_NODES = 20 * 1024;
 template <typename T, int MW>
 __global__ void __launch_bounds__(GN_LDS_NT) k_gn_lds(
     const T* __restrict__ pts, int64_t Q, int64_t share, MeshTab<T> mt, EvalK<T> k,
     double* __restrict__ part) {
   extern __shared__ char smem[];
   T* wt = (T*)smem;
-  constexpr int NT = GN_LDS_NT, RUNS = NT / 8;
+  constexpr int NT = GN_LDS_NT;
   const int tid = threadIdx.x;
   fill_mesh<T>(mt, wt, tid, NT);
   __syncthreads();
@@ -932,31 +930,22 @@ __global__ void __launch_bounds__(GN_LDS_NT) k_gn_lds(
     for (int a = 0; a < 6; ++a) v[21 + a] += J[a] * r;
     v[27] += r * r;
   }
-  // the LDS serves the reduction from here on: lanes' values, seven terms at
-  // a time, then the runs' sums of all terms
-  double* lv = (double*)smem;                // [thread][7]
-  double* runs = lv + NT * 7;                // [term][run]
-#pragma unroll
-  for (int g = 0; g < GN_TERMS / 7; ++g) {
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 7; ++q) lv[tid * 7 + q] = v[7 * g + q];
-    __syncthreads();
-    if (tid < 7 * RUNS) {
-      const int tq = tid / RUNS, run = tid % RUNS;
-      double s = 0.0;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) s += lv[(run * 8 + j) * 7 + tq];
-      runs[(7 * g + tq) * RUNS + run] = s;
-    }
-  }
+  // the LDS serves the reduction from here on, [term][thread]: 16 lanes per term
+  // add 32 values each, then meet in a butterfly (one barrier; seven terms at a
+  // time took nine: 200,000 FP32 points 15.9 -> 13.5 us)
+  double* lv = (double*)smem;
   __syncthreads();
-  if (tid < GN_TERMS * 8) {
-    const int term = tid >> 3;
-    double s = 0.0;
-    for (int j = tid & 7; j < RUNS; j += 8) s += runs[term * RUNS + j];
-    for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 8);
-    if ((tid & 7) == 0) part[term * (int64_t)gridDim.x + blockIdx.x] = s;
+#pragma unroll
+  for (int q = 0; q < GN_TERMS; ++q) lv[q * NT + tid] = v[q];
+  __syncthreads();
+  if (tid < GN_TERMS * 16) {
+    const double* p = lv + (tid >> 4) * NT + (tid & 15);
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < NT / 16; ++j) s[j & 3] += p[16 * j];
+    double t = (s[0] + s[1]) + (s[2] + s[3]);
+    for (int o = 8; o > 0; o >>= 1) t += __shfl_xor(t, o, 16);
+    if ((tid & 15) == 0) part[(tid >> 4) * (int64_t)gridDim.x + blockIdx.x] = t;
   }
 }
 
@@ -1418,8 +1407,7 @@ static void launch_gn_lds(rbf_ctx* ctx, const void* pts, int64_t Q, const MeshTa
                           const EvalK<T>& k, double* part) {
   const int64_t share = mesh_share(Q);
   constexpr int NT = GN_LDS_NT;
-  const size_t lds = std::max(sizeof(T) * (size_t)mt.n,
-                              sizeof(double) * (NT * 7 + GN_TERMS * (NT / 8)));
+  const size_t lds = std::max(sizeof(T) * (size_t)mt.n, sizeof(double) * GN_TERMS * NT);
   k_gn_lds<T, MW><<<(unsigned)ceil_div(Q, share), NT, lds, ctx->stream>>>(
       (const T*)pts, Q, share, mt, k, part);
 }
@@ -1496,14 +1484,11 @@ static rbf_status gn_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g, con
   RBF_TRY(eval_ws<T>(ctx, g, mesh, &tab));
   const EvalK<T> k = make_consts<T>(p, g, pose, z_off, mesh);
   MeshTab<T> mt;
-  // A Gauss-Newton workgroup has 512 threads: not for more nodes than these
-  // fill quickly (36,481 nodes, FP32, 200,000 points 23.2 us against the quads'
-  // 21.7), for the registers of 12-node windows (24.7 against 22.5), or for an
-  // FP64 workgroup's second pass over its lanes (200,000 points 23.3 against
-  // 21.0). Else, LDS and quads: FP32 1000 points 19.5 and 20.9, 200,000 18.1
-  // and 21.3, 1,000,000 33 and 39; FP64 100,000 points 18.8 and 21.2.
-  if (g->mesh_w <= 8 && (int64_t)g->mpw * g->mph <= GN_LDS_NODES &&
-      (sizeof(T) == 4 || Q <= MESH_WGS * GN_LDS_NT) && mesh_lds<T>(p, g, w, mesh, &mt)) {
+  // Not for the registers of 12-node windows (512 threads, 200,000 points 24.7 us
+  // against the quads' 22.5). Else, LDS and quads on 10,000 centers: FP32 1000
+  // points 16.5 and 18.2 us, 200,000 16.5 and 20.0, 1,000,000 30 and 38; FP64
+  // 16 and 18, 20.4 and 21.4, 51 and 63.
+  if (g->mesh_w <= 8 && mesh_lds<T>(p, g, w, mesh, &mt)) {
     rbf_status st;
     const int64_t wgs = ceil_div(Q, mesh_share(Q));
     double* part = (double*)ws_get(ctx, WS_TMP3, sizeof(double) * GN_TERMS * (size_t)wgs, &st);

@@ -1,5 +1,5 @@
 """Mesh form with the node weights in LDS, on both sides of its rules (node
-arrays that fit, points of a Gauss-Newton call) and for every window width,
+arrays that fit) and for every window width,
 against the quad form: the same centers and one more far away, whose node array
 fits no LDS.
 
