@@ -275,24 +275,28 @@ __device__ inline double4 TabReader<double>::load(int a, int off) const {
 
 // The same entries formed from the grid's arrays and the weights as they are
 // read: no packing launch, one more load behind the index. The operations are
-// those of k_pack_centers.
+// those of k_pack_centers. A slot behind the arrays' end has weight 0, as in the
+// packed table: its index reads 0, and `off` takes the weight's load out of its
+// resource (the weight of center 0 may not be finite, and phi = 0 would not mask
+// it). The first slot of a step lies in its run.
 template <typename T>
 struct RawReader {
   static constexpr bool AHEAD = true;
   using Out = typename Vec4<T>::type;
   struct Slot {
     double2 xy;
-    int32_t i;
+    int32_t i, off;
     double w;
   };
   __amdgpu_buffer_rsrc_t rc, ri, rw;
+  int32_t n;
   double x0, y0, ks;
-  __device__ RawReader(const double* ecxy, const int32_t* eidx, const double* w, int64_t n,
+  __device__ RawReader(const double* ecxy, const int32_t* eidx, const double* w, int64_t n_,
                        double x0_, double y0_, double ks_)
-      : x0(x0_), y0(y0_), ks(ks_) {
-    rc = __builtin_amdgcn_make_buffer_rsrc((void*)ecxy, (short)0, (int)(n * 16), 0x00020000);
-    ri = __builtin_amdgcn_make_buffer_rsrc((void*)eidx, (short)0, (int)(n * 4), 0x00020000);
-    rw = __builtin_amdgcn_make_buffer_rsrc((void*)w, (short)0, (int)(n * 8), 0x00020000);
+      : n((int32_t)n_), x0(x0_), y0(y0_), ks(ks_) {
+    rc = __builtin_amdgcn_make_buffer_rsrc((void*)ecxy, (short)0, (int)(n_ * 16), 0x00020000);
+    ri = __builtin_amdgcn_make_buffer_rsrc((void*)eidx, (short)0, (int)(n_ * 4), 0x00020000);
+    rw = __builtin_amdgcn_make_buffer_rsrc((void*)w, (short)0, (int)(n_ * 8), 0x00020000);
   }
   template <bool IDX>
   __device__ Slot fetch(int a, int u) const {
@@ -300,11 +304,12 @@ struct RawReader {
     s.xy = __builtin_bit_cast(double2,
                               __builtin_amdgcn_raw_buffer_load_b128(rc, a * 16 + u * 16, 0, 0));
     s.i = (int)__builtin_amdgcn_raw_buffer_load_b32(ri, a * 4 + u * 4, 0, 0);
+    s.off = u > 0 && a + u >= n ? INT32_MIN : 0;
     s.w = 0.0;
     return s;
   }
   __device__ void complete(Slot& s) const {
-    s.w = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rw, s.i * 8, 0, 0));
+    s.w = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rw, s.i * 8 | s.off, 0, 0));
   }
   __device__ Out value(const Slot& s) const {
 #pragma clang fp contract(off)

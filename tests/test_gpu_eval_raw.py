@@ -37,3 +37,30 @@ def test_raw_equals_packed(ctx, dtype, nx, ny, res, Q):
         for key, v in part.items():
             if v is not None:
                 assert torch.equal(v.view(bits), full[key][:Q].view(bits)), key
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("nx,ny", [(1, 1), (2, 1), (3, 3), (7, 5), (20, 20), (45, 31)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_non_finite_weight_stays_with_its_center(ctx, dtype, nx, ny, bad):
+    """A masked slot behind the arrays' end reads no weight: a weight that is
+    not finite, the first center's among them, reaches the same points in both
+    forms."""
+    p = api.Params()
+    rng = np.random.default_rng(nx)
+    c = synth.grid_centers(rng, nx, ny, 0.5, jitter=0.1)
+    grid = ctx.grid(p, dev(c))
+    n = LIMIT + 1
+    xy = rng.uniform(-1.0, [nx * 0.5 + 1.0, ny * 0.5 + 1.0], size=(n, 2))
+    pts = dev(xy).to(dtype)
+    bits = torch.int32 if dtype == torch.float32 else torch.int64
+    for at in {0, c.shape[0] // 2, c.shape[0] - 1}:
+        w = rng.normal(size=c.shape[0])
+        w[at] = bad
+        full = ctx.eval(p, grid, dev(w), pts)
+        part = ctx.eval(p, grid, dev(w), pts[:2001])
+        for key in ("f", "grad"):
+            a, b = part[key], full[key][:2001]
+            assert torch.equal(a.isnan(), b.isnan()), (at, key)
+            ok = ~a.isnan()
+            assert torch.equal(a[ok].view(bits), b[ok].view(bits)), (at, key)
