@@ -255,19 +255,19 @@ static rbf_status count_nodes(rbf_ctx* ctx, const double* xy, int64_t M, const M
   if (nc <= RADIUS_LDS_NODES && reach <= RADIUS_LDS_REACH && ((uintptr_t)xy & 15) == 0) {
     // 256 points per workgroup at least, one workgroup per CU at most
     const int wg = (int)std::max<int64_t>(1, std::min<int64_t>(RADIUS_LDS_WG, M / 256));
-    int32_t* part = cnt;
-    if (wg > 1) {
-      part = (int32_t*)ws_get(ctx, WS_SELECT, sizeof(int32_t) * nc * wg, &st);
-      if (!part) return st;
+    // without room for the planes the binned form below serves the call
+    int32_t* part =
+        wg > 1 ? (int32_t*)ws_try(ctx, WS_SELECT, sizeof(int32_t) * nc * wg) : cnt;
+    if (part) {
+      k_radius_lds<<<wg, 1024, sizeof(int32_t) * nc, ctx->stream>>>(xy, M, m, reach, r_kd * r_kd,
+                                                                    part);
+      RBF_LAUNCHED(ctx, "k_radius_lds");
+      if (wg > 1) {
+        k_radius_sum<<<ceil_div(nc, 64), 1024, 0, ctx->stream>>>(part, wg, (int)nc, cnt);
+        RBF_LAUNCHED(ctx, "k_radius_sum");
+      }
+      return RBF_OK;
     }
-    k_radius_lds<<<wg, 1024, sizeof(int32_t) * nc, ctx->stream>>>(xy, M, m, reach, r_kd * r_kd,
-                                                                  part);
-    RBF_LAUNCHED(ctx, "k_radius_lds");
-    if (wg > 1) {
-      k_radius_sum<<<ceil_div(nc, 64), 1024, 0, ctx->stream>>>(part, wg, (int)nc, cnt);
-      RBF_LAUNCHED(ctx, "k_radius_sum");
-    }
-    return RBF_OK;
   }
   const int32_t ext = reach;
   const int64_t ne = (int64_t)(m.nx + 2 * ext) * (m.ny + 2 * ext);
