@@ -107,9 +107,14 @@ __global__ void __launch_bounds__(256) k_radius_count(const double* __restrict__
 // 29 + 7 us, against 1.78 ms for binning them with device atomics and counting
 // per node (one thread per node walked about 1800 points alone). Bound by the
 // FP64 tests, 25 per point at r_kd <= res less the rows left out, and the LDS
-// adds.
+// adds. Every workgroup has an equal share of the points: lanes of a wave that
+// test the same node add to one address in turn, so full first and empty last
+// workgroups cost few points most (1000 on 20 x 20 nodes at a reach of 16: 231 ->
+// 110 us).
 constexpr int64_t RADIUS_LDS_NODES = 36 * 1024;  // 144 KB of counts
 constexpr int RADIUS_LDS_REACH = 16;
+constexpr int64_t RADIUS_LDS_FEW = 2048;       // fewer points than this:
+constexpr int64_t RADIUS_LDS_TESTS = 25 * 25;  // at most so many nodes tested by one
 constexpr int RADIUS_LDS_WG = 256;               // one workgroup of 16 waves per CU
 
 __global__ void __launch_bounds__(1024) k_radius_lds(const double* __restrict__ xy, int64_t M,
@@ -119,8 +124,9 @@ __global__ void __launch_bounds__(1024) k_radius_lds(const double* __restrict__ 
   const int nc = m.nx * m.ny;
   for (int e = threadIdx.x; e < nc; e += 1024) h[e] = 0;
   __syncthreads();
-  for (int64_t p = (int64_t)blockIdx.x * 1024 + threadIdx.x; p < M;
-       p += (int64_t)gridDim.x * 1024) {
+  const int64_t share = (M + gridDim.x - 1) / gridDim.x;
+  const int64_t end = min((blockIdx.x + 1) * share, M);
+  for (int64_t p = blockIdx.x * share + threadIdx.x; p < end; p += 1024) {
     const double2 q = *(const double2*)(xy + 2 * p);
     const double fx = floor((q.x - m.x0) / m.res), fy = floor((q.y - m.y0) / m.res);
     // also false for a coordinate that is not finite
@@ -251,8 +257,13 @@ static rbf_status count_nodes(rbf_ctx* ctx, const double* xy, int64_t M, const M
   // Counted in LDS where the mesh fits one CU's and a point's tests are few
   // enough for one lane. Whole calls, in LDS and binned: 2,000,000 points on
   // 101 x 101 nodes 81 us and 1.8 ms at a reach of 2 cells, 0.88 and 38 ms at
-  // 16; 500 points 51 and 96 at 2, 122 and 120 at 16, where the two meet.
-  if (nc <= RADIUS_LDS_NODES && reach <= RADIUS_LDS_REACH && ((uintptr_t)xy & 15) == 0) {
+  // 16. Few points do not hide the lane's tests: 30 on 40 x 40 nodes 78 and 80 at
+  // 12, 84 and 79 at 13 (729 nodes), 108 and 81 at 16; but on 8 x 8 nodes 40 and
+  // 83 at any. 2000 are ahead everywhere.
+  const int64_t side = 2 * (int64_t)reach + 1;
+  const int64_t tests = std::min<int64_t>(side, m.nx) * std::min<int64_t>(side, m.ny);
+  if (nc <= RADIUS_LDS_NODES && reach <= RADIUS_LDS_REACH &&
+      (M >= RADIUS_LDS_FEW || tests <= RADIUS_LDS_TESTS) && ((uintptr_t)xy & 15) == 0) {
     // 256 points per workgroup at least, one workgroup per CU at most
     const int wg = (int)std::max<int64_t>(1, std::min<int64_t>(RADIUS_LDS_WG, M / 256));
     // without room for the planes the binned form below serves the call

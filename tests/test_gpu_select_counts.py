@@ -32,3 +32,17 @@ def test_counts(ctx, nx, ny, r, n, shift):
         for thr in (0, 2):
             got = host(ctx.select_centers(q, roi, 0.5, r, thr, O.RADIUS))
             assert np.array_equal(got, O.select_centers(xy, roi, 0.5, r, thr, O.RADIUS))
+
+
+@pytest.mark.parametrize("nx,ny,r", [(40, 33, 5.5), (40, 33, 5.6), (25, 24, 7.4),
+                                     (26, 25, 7.4), (16, 16, 7.4)])
+@pytest.mark.parametrize("n", [30, 511, 1025, 2047, 2048])
+def test_counts_of_few_points(ctx, nx, ny, r, n):
+    """Reach 12 to 16 cells, with meshes on both sides of the nodes that a
+    point may test where there are few of them."""
+    rng = np.random.default_rng(n)
+    xy = rng.uniform([-4.5, -4.5], [0.5 * nx + 4.5, 0.5 * ny + 4.5], size=(n, 2))
+    roi = (0.0, 0.0, 0.5 * nx, 0.5 * ny)
+    for thr in (0, n // 3):
+        got = host(ctx.select_centers(dev(xy), roi, 0.5, r, thr, O.RADIUS))
+        assert np.array_equal(got, O.select_centers(xy, roi, 0.5, r, thr, O.RADIUS))
