@@ -201,10 +201,14 @@ void prof_end(rbf_ctx* ctx, int kind) {
 
 constexpr int SORT_CHUNK = 1024;
 constexpr int SORT_CHUNK_SMALL = 256;
-// Count tables of at most this many entries use small chunks: the scatter's
-// comparisons fall by four (10,000 items 18.6 -> 5.4 us) and the table stays
-// small; beyond, filling and scanning it costs more than that.
+// Up to SORT_SMALL_N items with a count table of at most SORT_SMALL_TABLE entries
+// use small chunks: the scatter's comparisons fall by four (10,000 items 18.6 ->
+// 5.4 us). Beyond, the column scan, one thread per key, walks more chunks than
+// that saves. Whole sorts on 20 x 20 centers, small and large chunks: 30,000
+// points 29.7 and 32.9 us, 50,000 36 and 35, 131,000 66 and 45, 3,000,000 1197
+// and 516; the same line on 60 x 60 and 200 x 200.
 constexpr int64_t SORT_SMALL_TABLE = (int64_t)1 << 20;
+constexpr int64_t SORT_SMALL_N = 48 * 1024;
 
 template <int CHUNK>
 __global__ void __launch_bounds__(256) k_sort_count(const int32_t* __restrict__ keys,
@@ -274,7 +278,8 @@ __global__ void __launch_bounds__(CHUNK) k_sort_scatter(const int32_t* __restric
 // count table has nchunks x nkeys entries.
 static rbf_status counting_sort(rbf_ctx* ctx, const int32_t* keys, int64_t n, int32_t nkeys,
                                 int32_t* perm, int32_t* start) {
-  const bool small = ceil_div(n, SORT_CHUNK_SMALL) * (int64_t)nkeys <= SORT_SMALL_TABLE;
+  const bool small = n <= SORT_SMALL_N &&
+                     ceil_div(n, SORT_CHUNK_SMALL) * (int64_t)nkeys <= SORT_SMALL_TABLE;
   const int64_t nchunks = n > 0 ? ceil_div(n, small ? SORT_CHUNK_SMALL : SORT_CHUNK) : 1;
   rbf_status st;
   int32_t* counts = (int32_t*)ws_get(ctx, WS_SORT2,

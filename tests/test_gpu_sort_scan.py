@@ -40,6 +40,27 @@ def test_sort_is_stable(ctx, n, m):
     assert np.all(pm[order] < pm[order + 1])
 
 
+@pytest.mark.parametrize("m", [49_151, 49_152, 49_153, 131_073])
+@pytest.mark.parametrize("n", [3, 20, 100])
+def test_sort_on_both_sides_of_the_chunk_rule(ctx, n, m):
+    p = api.Params()
+    rng = np.random.default_rng(m)
+    grid = ctx.grid(p, dev(synth.grid_centers(rng, n, n, 0.5, jitter=0.0)))
+    xy = rng.uniform(0.0, 0.5 * n, size=(m, 2))
+    xo, _, perm = ctx.sort_points(grid, dev(xy))
+    pm = host(perm)
+    assert np.array_equal(np.sort(pm), np.arange(m)) and np.array_equal(host(xo), xy[pm])
+    # sorting the sorted points changes nothing, and ties keep their order
+    assert np.array_equal(host(ctx.sort_points(grid, xo)[2]), np.arange(m))
+    h = p.cutoff * p.sigma * (1.0 + 1e-3)
+    q = (xy[pm] - (0.25 - h)) / h  # bins of the grid; points on an edge left out
+    cell = np.clip(np.floor(q), 0, [grid.nbx - 1, grid.nby - 1])
+    key = cell[:, 1] * grid.nbx + cell[:, 0]
+    ok = np.abs(q - np.rint(q)).min(1) > 1e-9
+    assert np.all(np.diff(key[ok]) >= 0)
+    assert np.all(np.diff(pm[ok])[np.diff(key[ok]) == 0] > 0)
+
+
 @pytest.mark.parametrize("n", [1, 63, 1024, 8191, 8192, 8193, 16_385, 40_000])
 def test_prefix_sums(ctx, n):
     xy = np.stack([0.5 * np.arange(n) + 0.25, np.full(n, 0.25)], 1)
