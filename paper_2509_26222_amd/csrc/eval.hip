@@ -1539,11 +1539,16 @@ static rbf_status adjoint_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g
                             const double* w, const void* pts, int64_t Q, int32_t dim,
                             const double* pose, const void* gf, const void* gr, void* d_pts,
                             double* d_w, double* d_pose, const double* dpose = nullptr) {
-  // Planes when the sums fit the LDS and the points outweigh clearing, writing
-  // and adding up N sums per plane. Whole calls by planes and by atomics:
-  // N = 400, 2048 points 24 and 24 us, 8192 21 and 66; N = 10,000, 8192
-  // points 20 and 18, 20,000 22 and 27, 200,000 43 and 184; N = 17,956,
-  // 20,000 points 27 and 26, 50,000 34 and 51 (FP32).
+  // Planes when the sums fit the LDS and the additions, about pi N / (bins with
+  // centers) for a point, outweigh clearing, writing and adding up N sums per plane and a launch.
+  // Few centers meet where more atomics fall on each of them, many where the
+  // planes' traffic is covered. Whole calls by planes and by atomics, centers 0.5 m
+  // and 1 m apart at a support of 1.5 m (28 and 7 additions): N = 400, 4096 points
+  // 19 and 28 us, at 1 m 18 and 17; N = 3600, 10,800 20 and 18, 21,600 21 and 25;
+  // N = 10,000, 20,000 points 21 and 24, at 1 m 20 and 16, 90,000 32 and 41;
+  // N = 17,956, 53,868 points 34 and 47, at 1 m 33 and 27. Of 630 such pairs (3 to
+  // 113 additions, 0.25 m to 1.5 m apart) none is slower by this rule than by
+  // atomics by more than the runs differ.
   // The buffer's size depends on the grid alone, so that it grows with the
   // grid's size only, as the table's; not taken if it would grow during a
   // capture.
@@ -1555,7 +1560,11 @@ static rbf_status adjoint_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g
   const bool mesh = sizeof(T) == 8 && g->mesh_w > 0 && g->mesh_w <= 8 && nodes <= ADJ_LDS_N;
   const int64_t n = mesh ? nodes : g->N;
   double* plane = nullptr;  // the planes, and behind them the mesh form's node weights
-  if (d_w && n <= ADJ_LDS_N && planes >= ADJ_MIN_PLANES && Q >= 2 * g->N)
+  const double adds =  // and the point itself; the outer bins hold no centers
+      (double)Q * (1.0 + 3.14 * (double)g->N / ((double)(g->nbx - 2) * (g->nby - 2)));
+  const bool enough =
+      Q >= 2 * g->N && adds >= std::min(140.0 * g->N, 250e3 + 30.0 * g->N);
+  if (d_w && n <= ADJ_LDS_N && planes >= ADJ_MIN_PLANES && enough)
     plane = (double*)ws_try(ctx, WS_ADJ, sizeof(double) * (ADJ_PLANES + 1) * n);
   const int form = plane && mesh ? g->mesh_w : 0;
   void* tab = plane ? plane + ADJ_PLANES * n : nullptr;

@@ -122,3 +122,16 @@ def test_mesh_planes(ctx, dim, res, nx, ny, Q):
         far = pts[3:5].abs().sum() * (float(gr[3:5].abs().max()) + 1.0)
         lim = Q * 4 * 300 * EPS * (size + 4.0) * reach + 16 * EPS * float(far)
         assert np.all(np.abs(host(dpose) - host(rpose)) <= lim)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("n,Q", [(30, 4200), (30, 4400), (70, 12_500), (70, 14_000)])
+def test_both_sides_of_the_additions_rule(ctx, dtype, n, Q):
+    test_planes_match_atomics(ctx, dtype, 3, n, 0, Q)
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("Q", [15_000, 16_500])
+def test_mesh_planes_of_sparse_centers(ctx, dim, Q):
+    """Windows of 4 nodes, seven centers in a support: on both sides of the rule."""
+    test_mesh_planes(ctx, dim, 1.0, 30, 30, Q)
