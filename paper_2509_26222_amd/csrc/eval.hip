@@ -1327,12 +1327,21 @@ rbf_status eval_workspace(rbf_ctx* ctx, const rbf_grid* g) {
   return RBF_OK;
 }
 
-// Binned calls of at most this many points read the grid's arrays as they are.
-// Whole calls on 10,000 centers, so and packed: FP64 1000 points 13 and 17 us,
-// 64,000 15 and 17, 100,000 23 and 21; FP32 64,000 14 and 16, 100,000 21 and 18
-// (with a launch saved the smaller ones are bound by the host). Alone, 1000
-// FP64 points on 400 centers: 13.4 -> 9.3 us.
+// Binned calls of few points read the grid's arrays as they are. That saves a
+// launch, and forming the candidates anew for each point costs as much at some
+// number of points times candidates (about half of max_cand), less in FP32, whose
+// packed entries are half as large. Whole calls on 100 x 100 centers, so and packed
+// (waited for): 0.5 m apart FP32 1000 points 21 and 25 us, 32,000 23.5 and 25,
+// 50,000 27 and 26, FP64 64,000 29 and 30; 0.3 m apart FP32 16,000 25.6 and 27.5,
+// 32,000 28.9 and 27.3, 65,000 38.7 and 29.5, FP64 32,000 30 and 31, 50,000 38
+// and 36; 0.15 m apart FP32 1000 41 and 45, 4000 42 and 41, 65,000 92 and 44, FP64
+// 16,000 46 and 44.
 constexpr int64_t EVAL_RAW_Q = 65536;
+template <typename T>
+static bool raw_form(const rbf_grid* g, int64_t Q, bool mesh) {
+  constexpr int64_t lim = sizeof(T) == 8 ? 7000000 : 3800000;
+  return !mesh && Q <= EVAL_RAW_Q && (Q + 2000) * (int64_t)g->max_cand <= lim;
+}
 
 // The table of one call in `tab`: the mesh form's node weights if mesh,
 // else the packed (x', y', w, index) of the eval-sorted centers.
@@ -1445,7 +1454,7 @@ static rbf_status eval_direct(rbf_ctx* ctx, const rbf_params* p, const rbf_grid*
     prof_end(ctx, RBF_PROF_EVAL);
     return RBF_OK;
   }
-  const bool raw = !mesh && Q <= EVAL_RAW_Q;
+  const bool raw = raw_form<T>(g, Q, mesh);
   Nbr<T> nb;
   RBF_TRY(pack_nbr<T>(ctx, p, g, w, tab, mesh, raw, &nb));
   const unsigned blocks = (unsigned)ceil_div(Q * LPP, 256);
@@ -1512,7 +1521,7 @@ static rbf_status gn_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g, con
     RBF_LAUNCHED(ctx, "k_eval_gn_sum");
     return RBF_OK;
   }
-  const bool raw = !mesh && Q <= EVAL_RAW_Q;
+  const bool raw = raw_form<T>(g, Q, mesh);
   Nbr<T> nb;
   RBF_TRY(pack_nbr<T>(ctx, p, g, w, tab, mesh, raw, &nb));
   int64_t blocks = ceil_div(Q * LPP, 256);

@@ -64,3 +64,23 @@ def test_non_finite_weight_stays_with_its_center(ctx, dtype, nx, ny, bad):
             assert torch.equal(a.isnan(), b.isnan()), (at, key)
             ok = ~a.isnan()
             assert torch.equal(a[ok].view(bits), b[ok].view(bits)), (at, key)
+
+
+@pytest.mark.parametrize("dtype,lim", [(torch.float32, 3_800_000), (torch.float64, 7_000_000)])
+@pytest.mark.parametrize("nx,res", [(40, 0.15), (60, 0.3), (70, 0.5)])
+def test_both_sides_of_the_candidates_rule(ctx, dtype, lim, nx, res):
+    """The last call that reads the arrays and the first that packs them, by the
+    candidates of the grid."""
+    p = api.Params()
+    rng = np.random.default_rng(nx)
+    grid = ctx.grid(p, dev(synth.grid_centers(rng, nx, nx, res, jitter=0.1 * res)))
+    w = dev(rng.normal(size=grid.N))
+    pts = dev(rng.uniform(-0.5, nx * res + 0.5, size=(LIMIT + 1, 2))).to(dtype)
+    full = ctx.eval(p, grid, w, pts)
+    bits = torch.int32 if dtype == torch.float32 else torch.int64
+    last = min(lim // grid.max_candidates - 2000, LIMIT)
+    assert 1000 < last
+    for Q in (last, last + 1):
+        part = ctx.eval(p, grid, w, pts[:Q])
+        for key in ("f", "grad"):
+            assert torch.equal(part[key].view(bits), full[key][:Q].view(bits)), (Q, key)
