@@ -444,6 +444,33 @@ static rbf_status check_grid(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* 
   return RBF_OK;
 }
 
+// Whether the information matrix is formed by blocks: estimates of both forms' times
+// (us). The row-wise kernel pays for each row, and for the points in the bins around
+// it, once per 64 of its entries (about 1.2 max_cand); a small map's rows are on the
+// chip at once and wait for one row's points. The blocks pay for bins, rows, the
+// blocks' memory and, least, points, and for the launches of every strip. The
+// constants are fits to whole calls of both on lattices of 4 to 192,000 centers, 0.25 m to
+// 1.5 m apart, with 0.76 to 16 points per center, at a support of 1.5 m. Row-wise
+// and by blocks: 100 x 100 centers 0.5 m apart, 7600 points 173 and 109, at 1 m
+// 65 and 113, 40,000 points 145 and 141, 160,000 438 and 205; 16,000 x 1 at 0.5 m,
+// 12,160 points 90 and 172, 256,000 521 and 313; 10 x 10, 100 points 62 and 60.
+// More bins than centers (scattered ones) are mostly empty blocks; below 100 points
+// in all (77 on 10 x 10 centers: 52 and 60) and 3 / 4 per center the rows are ahead.
+static bool gram_by_blocks(const rbf_grid* g, int64_t M, int64_t ld, int64_t strips) {
+  const double N = (double)g->N, bins = (double)g->nbx * g->nby;
+  const double bx = g->nbx - 2, by = g->nby - 2;  // bins with centers
+  const double near = (double)M / (bx * by) * (3.0 - 2.0 / bx) * (3.0 - 2.0 / by);
+  const double read = near * std::ceil(g->max_cand / 56.0);
+  double rows = std::max(2.7e-3 * N + 0.09e-3 * N * read, 5.0 + 0.35 * read);
+  // a line of bins: rows of few entries leave most lanes without one
+  if (bx < 2 || by < 2) rows *= g->max_cand <= 16 ? 1.6 : g->max_cand <= 32 ? 1.3 : 1.0;
+  // each strip also gathers for the bins next to its own
+  const double next = strips > 1 ? 2.0 * strips * g->nbx : 0.0;
+  const double blocks = 30.0 * strips + 1.1 * (4.8e-3 * bins + 2.4e-3 * next + 1.1e-3 * N +
+                                               3.1e-6 * bx * by * ld * ld + 0.7e-3 * M);
+  return rows > blocks;
+}
+
 extern "C" {
 
 rbf_status rbf_assemble_phi(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g,
@@ -540,12 +567,8 @@ rbf_status rbf_assemble_gram(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* 
   const int64_t blk = sizeof(double) * ld * (ld + 1) + 4 * sizeof(int32_t);  // bytes per bin
   const int64_t strip = std::min<int64_t>(nbins, (int64_t)(GRAM_WS / blk));
   char* ws = nullptr;
-  // The blocks are read per entry of calH whatever the number of points, the
-  // row-wise kernel pays per point: 40,000 centers and 20,000 points 390 us by
-  // blocks (the whole call) against 364 row-wise, 40,000 points 400 against
-  // 630; 4,900 centers and 2,450 points 117 against 107. More bins than centers
-  // (scattered ones) are mostly empty blocks.
-  if (ld <= GRAM_RMAX && 4 * M >= 3 * N && nbins <= N)
+  if (ld <= GRAM_RMAX && M >= 100 && 4 * M >= 3 * N && nbins <= N &&
+      gram_by_blocks(g, M, ld, ceil_div(nbins, strip)))
     ws = (char*)ws_try(ctx, WS_GRAM, (size_t)(strip * blk));
   if (!ws) {  // or no room for the blocks
     k_gram_values<<<ceil_div(N, 4), 256, 0, ctx->stream>>>(

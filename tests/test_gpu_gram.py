@@ -95,3 +95,16 @@ def test_accumulates_and_non_finite_height(ctx):
     hit = O.regressor_dense(xy[7:8], c, p.sigma, p.cutoff, p.sigma_eps)[0] > 0
     assert np.array_equal(np.isnan(bn), hit)
     assert np.array_equal(vn, host(v1)) and np.array_equal(bn[~hit], host(b1)[~hit])
+
+
+@pytest.mark.parametrize("nx,ny,res,m", [
+    (30, 30, 1.0, 2000), (30, 30, 1.0, 9000), (400, 1, 0.5, 350), (400, 1, 0.5, 12_000),
+    (2, 300, 0.5, 700), (2, 300, 0.5, 15_000), (10, 10, 0.5, 99), (10, 10, 0.5, 100),
+    (1, 1, 0.5, 900), (2, 2, 0.5, 64)])
+def test_both_sides_of_the_estimates(ctx, nx, ny, res, m):
+    """Sparse and thin lattices and small ones, with few points (row-wise) and
+    with many (by blocks)."""
+    rng = np.random.default_rng(m)
+    c = synth.grid_centers(rng, nx, ny, res, jitter=0.1 * res)
+    xy = rng.uniform(-0.5, [nx * res + 0.5, ny * res + 0.5], size=(m, 2))
+    check(ctx, api.Params(), c, xy, rng.normal(size=m))
