@@ -107,18 +107,18 @@ __global__ void __launch_bounds__(256) k_upd_rows(const double* __restrict__ xy,
 }
 
 // U^T[b, n] = sum_k vals[b,k] P[cols[b,k], n]  (P symmetric: rows of P) for the
-// rows b0, b0 + step, ... < b1 (uniform in the workgroup) and this thread's
-// columns n0, n0 + 256, n0 + 512, n0 + 768.
+// rows b0, b0 + step, ... < b1 (uniform in the wave) and this thread's columns
+// n0, n0 + W, ... (C of them), E entries of a row in flight together.
+template <int C, int W, int E>
 __device__ __forceinline__ void gather_u_rows(const double* __restrict__ P, int64_t ldp,
     int64_t N, int32_t Bc, int32_t Bp, const double* __restrict__ vals,
     const int32_t* __restrict__ cols, const int32_t* __restrict__ nnz, double* __restrict__ Ut,
     int64_t ldu, int64_t n0, int b0, int b1, int step) {
-  constexpr int C = 4, E = 4;  // columns; entries of a row in flight together
   int64_t n[C];
 #pragma unroll
-  for (int u = 0; u < C; ++u) n[u] = min(n0 + 256 * u, N - 1);
+  for (int u = 0; u < C; ++u) n[u] = min(n0 + W * u, N - 1);
   for (int b = b0; b < b1; b += step) {
-    double acc[C] = {0, 0, 0, 0};
+    double acc[C] = {};
     const int nz = b < Bc ? nnz[b] : 0;
     int q = 0;
     for (; q + E <= nz; q += E) {
@@ -144,7 +144,7 @@ __device__ __forceinline__ void gather_u_rows(const double* __restrict__ P, int6
     }
 #pragma unroll
     for (int u = 0; u < C; ++u)
-      if (n0 + 256 * u < N) Ut[(int64_t)b * ldu + n[u]] = acc[u];
+      if (n0 + W * u < N) Ut[(int64_t)b * ldu + n[u]] = acc[u];
   }
 }
 
@@ -155,8 +155,9 @@ __device__ __forceinline__ void upd_gather_u_body(const double* __restrict__ P, 
     const int32_t* __restrict__ cols, const int32_t* __restrict__ nnz, double* __restrict__ Ut,
     int64_t ldu, const int32_t* __restrict__ status, int64_t seq) {
   if (seq_skip(status, seq)) return;
-  gather_u_rows(P, ldp, N, Bc, Bp, vals, cols, nnz, Ut, ldu,
-                (int64_t)blockIdx.x * 1024 + threadIdx.x, blockIdx.y * 8, blockIdx.y * 8 + 8, 1);
+  gather_u_rows<4, 256, 4>(P, ldp, N, Bc, Bp, vals, cols, nnz, Ut, ldu,
+                           (int64_t)blockIdx.x * 1024 + threadIdx.x, blockIdx.y * 8,
+                           blockIdx.y * 8 + 8, 1);
 }
 
 __global__ void __launch_bounds__(256) k_upd_gather_u(const double* __restrict__ P, int64_t ldp,
@@ -267,16 +268,16 @@ __device__ __forceinline__ void gather_mfma_body(const double* __restrict__ P, i
   const double* H = gH + (int64_t)g * Rcap * 64;
   const int R4 = gR[g];
   if (R4 > GATHER_GROUP_RMAX) {
-    // row by row (uniform per workgroup), in the blocks of upd_gather_u_body: the
-    // workgroups of 1024 columns, eight of them but for the last run, take the
-    // group's 64 rows in turn. 4096 unsorted points, 5041 centers, batches of 64
-    // (with upd_S_rows): 14.6 ms; 50.5 with one column and one load in flight per
-    // thread and one workgroup per block of S; 28.2 with k_upd_gather_u and k_upd_S
-    // launched behind the grouped kernels.
-    const int x0 = blockIdx.x & ~7, j = blockIdx.x - x0;
-    const int nw = min(8, (int)((N + 127) / 128) - x0);
-    gather_u_rows(P, ldp, N, Bc, Bp, vals, cols, nnz, Ut, ldu, (int64_t)x0 * 128 + threadIdx.x,
-                  64 * g + j, 64 * g + 64, nw);
+    // row by row (uniform per workgroup): wave w takes the rows w, w + 4, ... of
+    // the group for the workgroup's 128 columns, 16 loads in flight per thread; the
+    // groups' workgroups of the same columns read the same part of P. 4096 unsorted
+    // points, 5041 centers, batches of 64 (with upd_S_rows): 15.6 ms; 50.5 with one
+    // load in flight and one workgroup per block of S; 28.2 with k_upd_gather_u and
+    // k_upd_S launched behind the grouped kernels. 24 unsorted patches in a plan:
+    // 20.6, 28.3 and 24.7 ms.
+    gather_u_rows<2, 64, 8>(P, ldp, N, Bc, Bp, vals, cols, nnz, Ut, ldu,
+                            (int64_t)blockIdx.x * 128 + lane,
+                            64 * g + __builtin_amdgcn_readfirstlane(wave), 64 * g + 64, 4);
     return;
   }
   v4d acc[4][2];
@@ -390,46 +391,51 @@ __global__ void __launch_bounds__(256) k_upd_S(const double* __restrict__ vals,
   upd_S_body(vals, cols, nnz, Ut, ldu, Bc, Bp, R, S, status, seq);
 }
 
-// Block (ga, gb) of S row by row, for the grouped kernel below: the workgroups
-// blockIdx.y = 0 .. S_ROWS_WG - 1 of the block share its columns, a thread has one
-// row a and 64 / (4 S_ROWS_WG) columns, whose values it gathers together for four
-// regressor entries at a time. The sums are upd_S_entry's.
-constexpr int S_ROWS_WG = 4;
+// Block (ga, gb) of S row by row, for the grouped kernel below: a thread has one
+// row a and, in each of the parts part0 <= part < S_ROWS_PARTS in steps of `step`,
+// four columns, whose values it gathers together for four regressor entries at a
+// time. The sums are upd_S_entry's. The parts of a single call's block are spread
+// over workgroups (blockIdx.y), which spread over the chip; the jobs of a round fill
+// it with one per block, and three more that find nothing to do would take 10 us a
+// round (24 patches 10.53 -> 10.59 ms).
+constexpr int S_ROWS_PARTS = 4;
 __device__ __forceinline__ void upd_S_rows(const double* __restrict__ vals,
     const int32_t* __restrict__ cols, const int32_t* __restrict__ nnz,
     const double* __restrict__ Ut, int64_t ldu, int32_t Bc, int32_t Bp, double R,
-    double* __restrict__ S, int ga, int gb) {
-  constexpr int NC = 4 * S_ROWS_WG, C = 64 / NC, E = 4;  // columns b0, b0 + NC, ...
+    double* __restrict__ S, int ga, int gb, int part0, int step) {
+  constexpr int NC = 4 * S_ROWS_PARTS, C = 64 / NC, E = 4;  // columns b0, b0 + NC, ...
   const int a = 64 * ga + (threadIdx.x & 63);
-  const int b0 = 64 * gb + 4 * blockIdx.y + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  double s[C];
-#pragma unroll
-  for (int i = 0; i < C; ++i) s[i] = (a == b0 + NC * i) ? R : 0.0;
   const int nz = a < Bc ? nnz[a] : 0;
-  for (int q = 0; q < nz; q += E) {
-    double v[E], u[E][C];
-    int32_t c[E];
+  for (int part = part0; part < S_ROWS_PARTS; part += step) {
+    const int b0 = 64 * gb + 4 * part + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double s[C];
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int64_t at = (int64_t)min(q + e, nz - 1) * Bp + a;
-      c[e] = cols[at];
-      v[e] = vals[at];
+    for (int i = 0; i < C; ++i) s[i] = (a == b0 + NC * i) ? R : 0.0;
+    for (int q = 0; q < nz; q += E) {
+      double v[E], u[E][C];
+      int32_t c[E];
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int64_t at = (int64_t)min(q + e, nz - 1) * Bp + a;
+        c[e] = cols[at];
+        v[e] = vals[at];
+      }
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+#pragma unroll
+        for (int i = 0; i < C; ++i) u[e][i] = Ut[(int64_t)(b0 + NC * i) * ldu + c[e]];
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (q + e < nz)
+#pragma unroll
+          for (int i = 0; i < C; ++i) s[i] += v[e] * u[e][i];
     }
 #pragma unroll
-    for (int e = 0; e < E; ++e)
-#pragma unroll
-      for (int i = 0; i < C; ++i) u[e][i] = Ut[(int64_t)(b0 + NC * i) * ldu + c[e]];
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (q + e < nz)
-#pragma unroll
-        for (int i = 0; i < C; ++i) s[i] += v[e] * u[e][i];
-  }
-#pragma unroll
-  for (int i = 0; i < C; ++i) {
-    const int b = b0 + NC * i;
-    if (b <= a)
-      S[(int64_t)a * Bp + b] = a < Bc && b < Bc ? s[i] : (a == b ? 1.0 : 0.0);
+    for (int i = 0; i < C; ++i) {
+      const int b = b0 + NC * i;
+      if (b <= a)
+        S[(int64_t)a * Bp + b] = a < Bc && b < Bc ? s[i] : (a == b ? 1.0 : 0.0);
+    }
   }
 }
 
@@ -439,9 +445,9 @@ __device__ __forceinline__ void upd_S_rows(const double* __restrict__ vals,
 // MFMA (wave w: columns 16w..16w+15, all 64 rows). It also clears its two
 // blocks of L^{-1}^T, which start at zero in every batch (they accumulate
 // partial sums): stores beside the loads that this kernel waits for, where a
-// launch of their own took 3 to 5 us. Grid: (blocks, S_ROWS_WG), where all but
-// the first of a block's workgroups have work only in a group whose distinct rows
-// are too many for the grouped data (see upd_S_rows): unsorted points.
+// launch of their own took 3 to 5 us. Grid: (blocks, 1 to S_ROWS_PARTS), where all
+// but the first of a block's workgroups have work only in a group whose distinct
+// rows are too many for the grouped data (see upd_S_rows): unsorted points.
 __device__ __forceinline__ void upd_S_groups_body(const int32_t* __restrict__ glist,
     const int32_t* __restrict__ gR, const double* __restrict__ gH, int64_t Rcap,
     const double* __restrict__ Ut, int64_t ldu, int32_t Bc, int32_t Bp, double R,
@@ -460,7 +466,7 @@ __device__ __forceinline__ void upd_S_groups_body(const int32_t* __restrict__ gl
   const double* H = gH + (int64_t)ga * Rcap * 64;
   const int R4 = gR[ga];
   if (R4 > GATHER_GROUP_RMAX)  // uniform per workgroup
-    upd_S_rows(vals, cols, nnz, Ut, ldu, Bc, Bp, R, S, ga, gb);
+    upd_S_rows(vals, cols, nnz, Ut, ldu, Bc, Bp, R, S, ga, gb, blockIdx.y, gridDim.y);
   if (blockIdx.y > 0) return;
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
@@ -1558,7 +1564,7 @@ rbf_status update_run(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g,
     prof_end(ctx, RBF_PROF_GATHER);
     if (ws.gH) {
       const int ng = Bpc / 64;
-      k_upd_S_groups<<<dim3(ng * (ng + 1) / 2, S_ROWS_WG), 256, 0, ctx->stream>>>(
+      k_upd_S_groups<<<dim3(ng * (ng + 1) / 2, S_ROWS_PARTS), 256, 0, ctx->stream>>>(
           ws.glist, ws.gR, ws.gH, ws.Rcap, Ut, ldu, Bc, Bpc, p->R, S, ws.LiT, vals, cols, nnz,
           ctx->d_status, sq);
       RBF_LAUNCHED(ctx, "k_upd_S_groups");
@@ -1944,7 +1950,7 @@ rbf_status update_round_grouped(rbf_ctx* ctx, const GRound& r, rbf_prec prec) {
     RBF_LAUNCHED(ctx, "k_upd_gather_u_g");
   }
   if (r.sg_x > 0) {
-    k_upd_S_groups_g<<<dim3(r.sg_x, S_ROWS_WG, nz), 256, 0, s>>>(r.jobs);
+    k_upd_S_groups_g<<<dim3(r.sg_x, 1, nz), 256, 0, s>>>(r.jobs);
     RBF_LAUNCHED(ctx, "k_upd_S_groups_g");
   }
   if (r.s_x > 0) {

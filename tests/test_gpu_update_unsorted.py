@@ -1,7 +1,7 @@
 """Groups of batch rows with more than 512 distinct rows of P (points in no
 order, or few points over a large map), which the grouped kernels take row by
-row: at the edges of their blocks (1024 columns shared by up to eight
-workgroups, batches that are no multiple of 64), and their time.
+row: at the edges of their blocks (128 columns, batches that are no multiple
+of 64), in one call and in a plan, and their time.
 
 Reference: the dense Kalman step in numpy. Tolerance: the step is backward
 stable, with cond(S) of the reference: 16 n eps cond(S) of what is
@@ -46,11 +46,41 @@ def test_rows_block_edges(ctx, nx, ny, m):
     assert np.abs(host(w) - w1).max() <= tol * (np.abs(w0).max() + np.abs(z).max()) * 10
 
 
+def test_rows_in_a_plan(ctx):
+    """The plan's form of the same kernels, one workgroup per block of S: equal
+    to the plain calls bit for bit."""
+    p = api.Params()
+    got = {}
+    for form in ("plain", "plan"):
+        patches = []
+        for q, (nx, ny, m) in enumerate([(27, 26, 300), (33, 31, 190), (8, 9, 120)]):
+            rng = np.random.default_rng(q)
+            grid = ctx.grid(p, dev(synth.grid_centers(rng, nx, ny, 0.5, jitter=0.1)))
+            xy = dev(rng.uniform(0.0, [0.5 * nx, 0.5 * ny], size=(m, 2)))
+            z = dev(rng.normal(0.0, 0.1, m))
+            w = torch.zeros(grid.N, dtype=torch.float64, device="cuda")
+            P = torch.eye(grid.N, dtype=torch.float64, device="cuda") * (p.R / p.lam)
+            pts = torch.cat([xy, z[:, None]], 1).contiguous()
+            patches.append(dict(grid=grid, w=w, P=P, xy=xy, z=z, pts=pts, batch=128,
+                                pose=(np.eye(3), np.zeros(3)), f=torch.empty_like(z)))
+        if form == "plan":
+            plan = api.Batched(ctx, p, patches, eval_prec="f64")
+            plan.run()
+            plan.sync()
+            plan.close()
+        else:
+            for q in patches:
+                ctx.update(p, q["grid"], q["w"], q["P"], q["xy"], q["z"], batch=128)
+        got[form] = [(host(q["w"]), host(q["P"])) for q in patches]
+    for a, b in zip(got["plain"], got["plan"]):
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
 def test_rows_time(ctx):
     """4096 points on 5041 centers in batches of 64, unsorted against sorted:
     28.2 and 13.0 ms with row-wise launches of their own, 50.5 and 10.8 where
-    the fallback had one workgroup per block of S and one load in flight, 14.6
-    and 10.8 as it is. The bound lies between these ratios (2.2, 4.7, 1.35)."""
+    the fallback had one workgroup per block of S and one load in flight, 15.6
+    and 10.8 as it is. The bound lies between these ratios (2.2, 4.7, 1.45)."""
     p = api.Params()
     rng = np.random.default_rng(2)
     grid = ctx.grid(p, dev(synth.grid_centers(rng, 71, 71, 0.5, jitter=0.0)))
