@@ -80,7 +80,13 @@ typedef struct rbf_grid rbf_grid; /* neighbour-binned copy of a center set  */
 /* ------------------------------------------------------------------ ctx */
 
 /* Create a context on HIP device `device`, enqueuing on `hip_stream`
- * (a hipStream_t; NULL = the null stream). *out receives the handle. */
+ * (a hipStream_t; NULL = the null stream). *out receives the handle.
+ * A context keeps the workspaces of its largest calls until it is destroyed.
+ * Three of them serve faster forms only: at most 144 MiB for
+ * rbf_assemble_gram, 43 MB for the adjoints of calls with many points and
+ * 43 MB for rbf_select_centers(_grow) by radius. Where such a buffer cannot
+ * be allocated, or would have to grow while the stream captures, the call is
+ * served without it. */
 rbf_status rbf_ctx_create(rbf_ctx** out, int device, void* hip_stream);
 /* Destroy a context and free its workspace (synchronises its stream).
  * Batched and solve plans made on the context use its device and stream
@@ -207,7 +213,8 @@ rbf_status rbf_bin_centers(rbf_ctx* ctx, const double* centers, int64_t N,
  * rounding (the support test is taken on the same scaled squared
  * distance). So does rbf_eval_adjoint in FP64 where a call has enough points
  * to sum the weights' gradient on chip; else it and the assembly keep the
- * binned form.
+ * binned form. (A center at exactly the support's edge, where the test is a
+ * matter of rounding, may count in one form and not in the other.)
  * res = 0 returns the grid to the binned form. The dense node array covers
  * the centers' node range plus a margin of the window width: at most
  * 16384 nodes per axis and 2^26 in all; the support may span at most 12

@@ -28,6 +28,9 @@
 //     [L; L^{-T}], so these rows end as the rows of L^{-T}, scaled by
 //     1 / sqrt(pivot) (v_rsq_f64 and two Newton-Raphson steps) when they are
 //     stored. They run behind the chain and end about four groups after it.
+// Pivots, panel rows and inverse rows are scaled by reciprocals within 11 ulp
+// (rcp_nr); chol64_phased takes correctly rounded ones for the panel rows. All sums
+// are FP64 in both.
 // The waves wait for each other by progress words in LDS. A wave only ever
 // waits for an earlier panel or an earlier wave of the same panel, the
 // first chain waits for nothing, and all four waves of the workgroup are

@@ -968,7 +968,7 @@ __global__ void __launch_bounds__(GN_LDS_NT) k_gn_lds(
 // exponentials of the candidates and the LDS additions.
 constexpr int64_t ADJ_PLANES = 256;            // one workgroup per CU
 // Its threads: four waves per SIMD; three for the mesh form's 8-node windows,
-// whose FP64 registers do not fit four (200,000 points 42.6 -> 40.6 us).
+// whose FP64 registers do not fit four (200,000 points 42.0 -> 41.3 us).
 template <int MW>
 constexpr int adj_threads() { return MW == 8 ? 768 : 1024; }
 constexpr int64_t ADJ_LDS_N = 18 * 1024;       // 144 KB of sums
@@ -1392,7 +1392,9 @@ static void launch_eval(rbf_ctx* ctx, unsigned blocks, int32_t dim, const void* 
 // 256 threads only (200,000 points 34.8 us against the quads' 32.2). Whole
 // calls on 100 x 100 centers otherwise, LDS and quads: FP32 1000 points 17.0
 // and 20.2 us, 200,000 17.1 and 19.7, 1,000,000 26 and 42; FP64 16.9 and 19.3,
-// 18.9 and 20.8, 51 and 74.
+// 18.9 and 20.8, 51 and 74. (The kernels of 200,000 FP64 points: 17.7 us, with a
+// second pass that few lanes take, against 15.1 + 2.9 for the packing. Waited for,
+// from one point to 700,000, the LDS form is ahead or equal at every size.)
 template <typename T>
 static bool mesh_lds(const rbf_params* p, const rbf_grid* g, const double* w, bool mesh,
                      MeshTab<T>* mt) {
@@ -1558,9 +1560,8 @@ static rbf_status adjoint_t(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* g
   // N = 17,956, 53,868 points 34 and 47, at 1 m 33 and 27. Of 630 such pairs (3 to
   // 113 additions, 0.25 m to 1.5 m apart) none is slower by this rule than by
   // atomics by more than the runs differ.
-  // The buffer's size depends on the grid alone, so that it grows with the
-  // grid's size only, as the table's; not taken if it would grow during a
-  // capture.
+  // The buffer's size depends on the grid and the type alone, as the table's; not
+  // taken if it would grow during a capture.
   const int64_t planes = std::min<int64_t>(ADJ_PLANES, Q / 256);
   const int64_t nodes = (int64_t)g->mpw * g->mph;
   // In FP64 on a mesh with windows of up to 8 nodes (the registers of a 12-node

@@ -87,8 +87,8 @@ __device__ inline int64_t xcd_tile(int64_t bid, int64_t per_xcd) {
 // for bit.
 //
 // Rows past K and columns past the width: rows read as zero (out of the
-// resource), columns are read at the operand's last one and their results
-// not stored.
+// resource, whose range check counts the scalar offset, also one beyond the
+// range), columns are read at the operand's last one and their results not stored.
 template <int BM, int BN>
 struct Direct {  // loads in flight per wave, measured per block shape
   static constexpr int KU = BM * BN >= 8 ? 2 : BM * BN >= 4 ? 1 : 4;
