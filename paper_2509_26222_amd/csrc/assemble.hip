@@ -444,16 +444,19 @@ static rbf_status check_grid(rbf_ctx* ctx, const rbf_params* p, const rbf_grid* 
   return RBF_OK;
 }
 
-// Whether the information matrix is formed by blocks: estimates of both forms' times
-// (us). The row-wise kernel pays for each row, and for the points in the bins around
-// it, once per 64 of its entries (about 1.2 max_cand); a small map's rows are on the
-// chip at once and wait for one row's points. The blocks pay for bins, rows, the
-// blocks' memory and, least, points, and for the launches of every strip. The
-// constants are fits to whole calls of both on lattices of 4 to 192,000 centers, 0.25 m to
-// 1.5 m apart, with 0.76 to 16 points per center, at a support of 1.5 m. Row-wise
-// and by blocks: 100 x 100 centers 0.5 m apart, 7600 points 173 and 109, at 1 m
-// 65 and 113, 40,000 points 145 and 141, 160,000 438 and 205; 16,000 x 1 at 0.5 m,
-// 12,160 points 90 and 172, 256,000 521 and 313; 10 x 10, 100 points 62 and 60.
+// Whether the information matrix is formed by blocks: estimates of what each form
+// takes beyond the parts they share. The row-wise kernel pays for each row, and for the
+// points in the bins around it, once per 64 of its entries (about 1.2 max_cand); a small
+// map's rows are on the chip at once and wait for one row's points. The blocks pay for
+// bins, rows, the blocks' memory and, least, points, and for the launches of every strip.
+// The constants (one unit is near 2 us) are those that choose best, by the time lost to
+// the other form, over whole calls of both on 75 lattices of 100 to 193,600 centers,
+// 0.25 m to 1.4 m apart and down to one center wide, with 0.76 to 8 points per center,
+// at a support of 1.5 m: of 409 calls 4 take more than 1.08 times the faster form, at
+// most 1.17. Row-wise and by blocks, us: 100 x 100 centers 0.5 m apart, 7600 points 154
+// and 108, at 1 m 50 and 112, 40,000 points 132 and 141, 80,000 218 and 159; 60 x 60 at
+// 0.75 m, 5400 points 58 and 65, 14,400 104 and 72; 16,000 x 1 at 0.5 m, 12,160 points 59
+// and 172, 128,000 245 and 248; 10 x 10, 100 points 66 and 60.
 // More bins than centers (scattered ones) are mostly empty blocks; below 100 points
 // in all (77 on 10 x 10 centers: 52 and 60) and 3 / 4 per center the rows are ahead.
 static bool gram_by_blocks(const rbf_grid* g, int64_t M, int64_t ld, int64_t strips) {
@@ -461,13 +464,13 @@ static bool gram_by_blocks(const rbf_grid* g, int64_t M, int64_t ld, int64_t str
   const double bx = g->nbx - 2, by = g->nby - 2;  // bins with centers
   const double near = (double)M / (bx * by) * (3.0 - 2.0 / bx) * (3.0 - 2.0 / by);
   const double read = near * std::ceil(g->max_cand / 56.0);
-  double rows = std::max(2.7e-3 * N + 0.09e-3 * N * read, 5.0 + 0.35 * read);
+  double rows = std::max(1.4e-3 * N + 0.105e-3 * N * read, 3.0 + 0.22 * read);
   // a line of bins: rows of few entries leave most lanes without one
   if (bx < 2 || by < 2) rows *= g->max_cand <= 16 ? 1.6 : g->max_cand <= 32 ? 1.3 : 1.0;
   // each strip also gathers for the bins next to its own
   const double next = strips > 1 ? 2.0 * strips * g->nbx : 0.0;
-  const double blocks = 30.0 * strips + 1.1 * (4.8e-3 * bins + 2.4e-3 * next + 1.1e-3 * N +
-                                               3.1e-6 * bx * by * ld * ld + 0.7e-3 * M);
+  const double blocks = 9.0 * strips + 8.4e-3 * bins + 2.5e-3 * next + 1.1e-3 * N +
+                        2.9e-6 * bx * by * ld * ld + 0.35e-3 * M;
   return rows > blocks;
 }
 

@@ -108,3 +108,14 @@ def test_both_sides_of_the_estimates(ctx, nx, ny, res, m):
     c = synth.grid_centers(rng, nx, ny, res, jitter=0.1 * res)
     xy = rng.uniform(-0.5, [nx * res + 0.5, ny * res + 0.5], size=(m, 2))
     check(ctx, api.Params(), c, xy, rng.normal(size=m))
+
+
+@pytest.mark.parametrize("nx,ny,res,m", [
+    (60, 60, 0.75, 5400), (60, 60, 0.75, 14_400), (90, 40, 0.9, 2736), (90, 40, 0.9, 14_400),
+    (64, 64, 0.5, 3112), (2000, 2, 0.5, 3040), (2000, 2, 0.5, 16_000)])
+def test_lattices_near_the_estimates_line(ctx, nx, ny, res, m):
+    """Lattices on which the two forms take about as long: by rows and by blocks."""
+    rng = np.random.default_rng(m)
+    c = synth.grid_centers(rng, nx, ny, res, jitter=0.1 * res)
+    xy = rng.uniform(-0.5, [nx * res + 0.5, ny * res + 0.5], size=(m, 2))
+    check(ctx, api.Params(), c, xy, rng.normal(size=m))
